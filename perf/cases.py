@@ -33,8 +33,10 @@ MD_DT = 0.25  # fs
 FORCE_WEIGHT = 0.1
 
 
-def _case(name, kind, work, form, nx, ny, nz, spacing=SPACING, n=0, layout="padded"):
+def _case(name, kind, work, form, nx, ny, nz, spacing=None, n=0, layout="padded"):
     """n: MD steps or training boxes (the sides then bound the boxes' sides)."""
+    if spacing is None:
+        spacing = synth.NI_LATTICE if work in ("fcc", "wide") else SPACING
     return {"name": name, "kind": kind, "work": work, "form": form, "nx": nx, "ny": ny, "nz": nz,
             "spacing": spacing, "n": n, "layout": layout}
 
@@ -98,7 +100,7 @@ def draw(rng):
     small = 3 if lattice else 4
     top = int(most ** (1.0 / 3.0))
     s = [max(small, min(top, round(side * rng.uniform(0.8, 1.25)))) for _ in range(3)]
-    return {k: v for k, v in _case("", kind, work, form, *s, spacing if not lattice else synth.NI_LATTICE,
+    return {k: v for k, v in _case("", kind, work, form, *s, None if lattice else spacing,
                                    rng.randint(2, 6) if kind == "md" else 0,
                                    "index" if kind == "compute" and rng.random() < 0.1 else "padded").items()
             if k != "name"}
