@@ -60,6 +60,7 @@ struct nnp_handle {
   std::string err;
   double rc = 0.0;
   int variant = 0;                      // triplet-kernel instantiation (see launch_mode)
+  bool xpoly = false;                   // tab_d.xpoly reaches XP_MAX_ERROR for every angular eta
   std::vector<int> n_sf;                // per element
   std::vector<std::vector<int>> sizes;  // per element layer widths
   std::vector<double> params;           // flat caller layout
@@ -569,6 +570,7 @@ TripArgs<P> trip_args(nnp_handle* h, Common& cm) {
   t.nnb = cm.nnb;
   t.st = cm.d_st;
   t.tab = reinterpret_cast<const DevTab<typename Types<P>::T>*>(h->d_tab);
+  t.poly = h->xpoly ? 1 : 0;
   return t;
 }
 
@@ -1184,6 +1186,46 @@ nnp_status md_run(nnp_handle* h, int64_t n, void* pos_v, void* vel_v, void* f_v,
 }
 
 // --------------------------------------------------------------- create
+// Interpolates X(t) = (1 + cos(pi sqrt t)) / 2 e^{-b t} at the Chebyshev points
+// of [0, 1] (Newton's divided differences, then the monomial basis in t - 1/2,
+// in long double) to degree DEG and returns the largest error of the rounded
+// coefficients' polynomial on a fine grid.  At b = eta rc^2 = 1.08 (the water
+// table's larger eta) degree 14 is within 5e-17, and it passes XP_MAX_ERROR
+// near b = 1.35; degree 10 is enough below b = 0.04.  The exponential path's
+// cutoff polynomial alone is within 1.4e-15.  (Powers of t - 1/2, not of t: the
+// rounding of their coefficients is half as large and, unlike with powers of t,
+// leaves no common sign, which summed energies would show.)
+constexpr double XP_MAX_ERROR = 3e-16, XP_LOW_ERROR = 1.2e-16;
+template <int DEG>
+double fit_xpoly(double b, double* c) {
+  using L = long double;
+  const L pi = 3.14159265358979323846264338327950288L;
+  auto X = [&](L t) { return (1.0L + cosl(pi * sqrtl(t))) / 2.0L * expl(-(L)b * t); };
+  constexpr int N = DEG + 1;
+  L t[N], d[N], p[N] = {};  // t: the points, less 1/2
+  for (int i = 0; i < N; ++i) {
+    t[i] = cosl(pi * (i + 0.5L) / N) / 2.0L;
+    d[i] = X(t[i] + 0.5L);
+  }
+  for (int k = 1; k < N; ++k)
+    for (int i = N - 1; i >= k; --i) d[i] = (d[i] - d[i - 1]) / (t[i] - t[i - k]);
+  p[0] = d[N - 1];
+  for (int i = N - 2; i >= 0; --i) {  // p <- p (x - t_i) + d_i
+    for (int k = N - 1; k > 0; --k) p[k] = p[k - 1] - p[k] * t[i];
+    p[0] = d[i] - p[0] * t[i];
+  }
+  for (int i = 0; i <= XP_DEG; ++i) c[i] = i < N ? (double)p[i] : 0.0;
+  L worst = 0;
+  for (int g = 0; g <= 1000; ++g) {
+    const L x = g / 1000.0L;
+    L v = c[N - 1];
+    for (int i = N - 2; i >= 0; --i) v = v * (x - 0.5L) + (L)c[i];
+    const L e = fabsl(v - X(x));
+    if (!(e <= worst)) worst = e;  // NaN too
+  }
+  return (double)worst;
+}
+
 nnp_status build_table(nnp_handle* h, int n_el, int n_sf, const nnp_sf* sf, const nnp_net* nets) {
   DevTab<double>& t = h->tab_d;
   std::memset(&t, 0, sizeof(t));
@@ -1258,12 +1300,16 @@ nnp_status build_table(nnp_handle* h, int n_el, int n_sf, const nnp_sf* sf, cons
     }
   }
   int ne_max = 1;
+  h->xpoly = h->prec == NNP_FP64;
   for (int e = 0; e < n_el; ++e) {
     t.n_sf[e] = count[e];
     t.n_eta[e] = (int)etas[e].size();
     for (size_t x = 0; x < etas[e].size(); ++x) {
       t.aeta[e][x] = etas[e][x];
       t.aeta2[e][x] = etas[e][x] * 1.4426950408889634074;
+      const double b = etas[e][x] * h->rc * h->rc;
+      t.xhigh[e][x] = fit_xpoly<XP_LOW>(b, t.xpoly[e][x]) <= XP_LOW_ERROR ? 0 : 1;
+      if (t.xhigh[e][x] && !(fit_xpoly<XP_DEG>(b, t.xpoly[e][x]) <= XP_MAX_ERROR)) h->xpoly = false;
     }
     ne_max = std::max(ne_max, t.n_eta[e]);
   }

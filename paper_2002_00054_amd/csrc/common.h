@@ -15,7 +15,7 @@ constexpr int MAX_ANG = 8;                           // angular SFs per (centre,
 constexpr int MAX_NE = 4;                            // distinct angular eta per centre element
 constexpr int HID = 32;                              // padded hidden width and input width
 constexpr int LD = 32;                               // row stride of G, dE/dG and JVP rows
-constexpr int FC_DEG_MAX = 16;                       // storage bound of the cutoff polynomial
+constexpr int XP_DEG = 14, XP_LOW = 10;              // degrees of the per-eta r_jk polynomials (DevTab::xpoly)
 constexpr int WAVE = 64;
 constexpr int QCAP = 128;                            // per-wave triplet queue (stack of pairs)
 
@@ -74,6 +74,11 @@ struct DevTab {
   int n_eta[MAX_EL];
   T aeta[MAX_EL][MAX_NE];              // eta
   T aeta2[MAX_EL][MAX_NE];             // eta * log2(e)
+  // X_n = fc(r) e^{-eta_n r^2} as a polynomial in r^2/rc^2 - 1/2 (FP64 kernels;
+  // used only if every one of the table reaches XP_MAX_ERROR); xhigh: it has
+  // terms above degree XP_LOW
+  T xpoly[MAX_EL][MAX_NE][XP_DEG + 1];
+  int xhigh[MAX_EL][MAX_NE];
   // angular SFs, per (centre e, neighbour-pair class c).  Each SF is the
   // product of a basis function (1 + lambda cos)^zeta, basis index
   // q = 6 [lambda < 0] + log2 zeta, with a radial factor of exponent index n;
@@ -226,23 +231,26 @@ __device__ inline double rsqrt_t(double s) { return 1.0 / sqrt(s); }
 __device__ inline float rsqrt_t(float s) { return __builtin_amdgcn_rsqf(s); }
 
 // Cutoff polynomial in t = r^2/rc^2 per arithmetic type: interpolants of
-// fc = (1 + cos(pi sqrt(t)))/2 at the Chebyshev points, in the monomial basis
-// (gen_cutoff.py).  FP64: degree 10, max error 1.4e-15 (fc) and 1.7e-13
-// (dfc/dt).  FP32: degree 6, max error 5.5e-9, below FP32 rounding.  Both are
-// several terms shorter than the Taylor series of the same accuracy.
+// fc = (1 + cos(pi sqrt(t)))/2 at the Chebyshev points (gen_cutoff.py).  FP64:
+// degree 10 in powers of t - 1/2, max error 4e-17 (fc) and 4e-15 (dfc/dt)
+// before rounding.  FP32: degree 6 in powers of t, max error 5.5e-9, below
+// FP32 rounding.  Both are several terms shorter than the Taylor series of the
+// same accuracy.
 template <class T> struct FcPoly;
 template <> struct FcPoly<double> {
   static constexpr int D = 10;
+  __device__ static double variable(double s, double inv_rc2) { return __builtin_fma(s, inv_rc2, -0.5); }
   static constexpr double a(int n) {
-    constexpr double c[11] = {0.99999999999999867,    -2.4674011002721739,    2.0293560632041152,
-                              -0.66763138438064717,   0.11766531490754019,    -0.012903444753172158,
-                              0.00096478511035206918, -5.2316220181516193e-05, 2.1490610761661228e-06,
-                              -6.8101185620021584e-08, 1.44427758641541e-09};
+    constexpr double c[11] = {0.1971500664605933,      -0.88379293731319197,   1.1891487278891328,
+                              -0.46225817257593987,    0.088804902456443971,   -0.010269231077289678,
+                              0.00079602567959765269,  -4.4311202098710064e-05, 1.8587616141233574e-06,
+                              -6.0917656138878952e-08, 1.6020207321886072e-09};
     return c[n];
   }
 };
 template <> struct FcPoly<float> {
   static constexpr int D = 6;
+  __device__ static float variable(float s, float inv_rc2) { return s * inv_rc2; }
   static constexpr double a(int n) {
     constexpr double c[7] = {0.99999999447228860, -2.4674005583220304, 2.0293473727609408, -0.66757901115278839,
                              0.11751451131309654, -0.012679142877827992, 0.00079683910699860207};
@@ -263,7 +271,7 @@ struct Cutoff {
   }
   // fc and dfc/ds at s = r^2, for s < rc^2.
   __device__ inline void eval_in(T s, T& fc, T& dfc_ds) const {
-    const T t = s * inv_rc2;
+    const T t = FcPoly<T>::variable(s, inv_rc2);
     T f = T(FcPoly<T>::a(D)), g = T(D * FcPoly<T>::a(D));
 #pragma unroll
     for (int n = D - 1; n >= 1; --n) {
@@ -280,7 +288,7 @@ struct Cutoff {
     dfc_ds = in ? dfc_ds : T(0);
   }
   __device__ inline T value_in(T s) const {
-    const T t = s * inv_rc2;
+    const T t = FcPoly<T>::variable(s, inv_rc2);
     T f = T(FcPoly<T>::a(D));
 #pragma unroll
     for (int n = D - 1; n >= 0; --n) f = f * t + T(FcPoly<T>::a(n));
