@@ -78,9 +78,12 @@ typedef enum { NNP_FP64 = 0, NNP_FP32 = 1, NNP_BF16_MIXED = 2 } nnp_precision;
  *  centre    element of the centre atom, in [0, n_el)
  *  kind      2 = radial G2 (neighbour element nbr[0]);
  *            3 = narrow angular G3 (unordered neighbour-element pair nbr[0], nbr[1]);
- *            9 = wide angular G9 (same pair convention).  A table holding any
- *                G9 runs its SF, force and force-adjoint passes one thread per
- *                centre (the stored-Jacobian variant handles G9 directly).
+ *            9 = wide angular G9 (same pair convention).  In the FP64 and FP32
+ *                forms a table holding any G9 runs its passes one wave per
+ *                centre (nnp_set_parallelism's thread level is obeyed; its
+ *                two-wave level is not built for these tables); in the BF16
+ *                form, and where an atom's neighbours exceed the LDS of that
+ *                level, one thread per centre.
  *  eta       Gaussian exponent, A^-2, >= 0
  *  rs        radial shift, A (G2 only; must be 0 for G3 and G9)
  *  zeta      exponent, one of 1, 2, 4, 8, 16, 32 (G3 and G9 only)
@@ -287,7 +290,8 @@ int64_t nnp_md_list_builds(const nnp_handle* h);
  *                  LDS; the first stages the neighbours, then the two split
  *                  the walk over neighbour pairs and their SF sums are added.
  * NNP_PAR_WAVE or NNP_PAR_WAVE2 with such a batch is NNP_E_ARG, reported
- * before any SF or force kernel is launched.
+ * before any SF or force kernel is launched (with wide angular functions it
+ * takes the thread level instead).
  * Both give the same results up to rounding order; the force-adjoint pass of
  * nnp_backward follows the same choice.  An unknown mode is NNP_E_ARG.
  */
@@ -311,8 +315,9 @@ nnp_status nnp_set_parallelism(nnp_handle* h, int mode);
  *                    offset.
  * Results equal those of the padded layout up to rounding order.  The
  * thread-level passes, the stored-Jacobian form, the Verlet-skin MD path and
- * nnp_count_work always use the padded layout; a call that ends up at the
- * thread level rebuilds its list padded.  An unknown layout is NNP_E_ARG.
+ * nnp_count_work always use the padded layout, and so do tables with wide
+ * angular functions; a call that ends up at the thread level rebuilds its list
+ * padded.  An unknown layout is NNP_E_ARG.
  */
 typedef enum { NNP_LIST_PADDED = 0, NNP_LIST_INDEX = 1, NNP_LIST_COMPACT = 2 } nnp_list_layout;
 nnp_status nnp_set_list_layout(nnp_handle* h, int layout);

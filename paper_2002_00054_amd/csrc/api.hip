@@ -87,7 +87,8 @@ struct nnp_handle {
   std::vector<hipEvent_t> events;
   bool has_forward = false;
   int parallelism = NNP_PAR_AUTO;        // SF and force passes: wave or thread per centre
-  bool has_wide = false;                 // the table holds wide angular SFs (thread-per-centre passes only)
+  bool has_wide = false;                 // the table holds wide angular SFs
+  bool wide_flat = false;                // and its wave kernels do not take them (a wide SF given twice)
   int deriv_mode = NNP_DERIV_RECOMPUTE;
   // The last batch forward's inputs, for nnp_backward: while fwd_valid, the
   // workspace holds that forward's sorted order, neighbour list and G~ (and
@@ -268,6 +269,7 @@ DevTab<T> convert_tab(const DevTab<double>& s) {
     }
     for (int c = 0; c < MAX_CLS; ++c) {
       t.ang_cnt[e][c] = s.ang_cnt[e][c];
+      for (int k = 0; k < 2; ++k) t.ang_kind[e][c][k] = s.ang_kind[e][c][k];
       for (int k = 0; k < MAX_ANG; ++k) {
         t.ang_bit[e][c][k] = s.ang_bit[e][c][k];
         t.ang_pre[e][c][k] = (T)s.ang_pre[e][c][k];
@@ -279,6 +281,8 @@ DevTab<T> convert_tab(const DevTab<double>& s) {
       for (int b = 0; b < 12 * MAX_NE; ++b) {
         t.qn_out[e][c][b] = s.qn_out[e][c][b];
         t.qn_pre[e][c][b] = (T)s.qn_pre[e][c][b];
+        t.qw_out[e][c][b] = s.qw_out[e][c][b];
+        t.qw_pre[e][c][b] = (T)s.qw_pre[e][c][b];
       }
     for (int k = 0; k < MAX_SF; ++k) {
       t.shift_d[e][k] = s.shift_d[e][k];
@@ -632,8 +636,17 @@ nnp_status use_flat(nnp_handle* h, int mode_a, int mode_b, bool* flat, int* wpc 
               ? 2
               : 1;
   if (wpc) *wpc = w;
-  *flat = h->parallelism == NNP_PAR_THREAD || h->has_wide;
+  // Wide angular SFs stay at the thread level in the BF16 form: its outputs turn
+  // on the rounding of the hidden layer's inputs to BF16, and another order of
+  // the FP32 terms moves energies and forces by 5e-5 and 3e-4 (FP32: 3e-6).
+  *flat = h->parallelism == NNP_PAR_THREAD || h->wide_flat || (P == P_BF16 && h->has_wide);
   if (*flat) return NNP_OK;
+  if (h->has_wide) {  // one wave per centre, or the thread level for an atom beyond its LDS
+    if (wpc) *wpc = 1;
+    *flat = std::max(triplet_lds_bytes<P>(mode_a, h->variant, h->lcap, 1),
+                     triplet_lds_bytes<P>(mode_b, h->variant, h->lcap, 1)) > lds_limit();
+    return NNP_OK;
+  }
   auto lds_of = [&](int k) {
     return std::max(triplet_lds_bytes<P>(mode_a, h->variant, h->lcap, k),
                     triplet_lds_bytes<P>(mode_b, h->variant, h->lcap, k));
@@ -649,6 +662,15 @@ nnp_status use_flat(nnp_handle* h, int mode_a, int mode_b, bool* flat, int* wpc 
   }
   *flat = true;
   return NNP_OK;
+}
+
+// A wave-level pass of the given mode (0 SF, 1 force, 2 force-adjoint product).
+template <int P>
+void launch_wave(const nnp_handle* h, int mode, const TripArgs<P>& ta, hipStream_t stream) {
+  if constexpr (P != P_BF16) {
+    if (h->has_wide) return launch_triplet_wide<P>(mode, h->variant, ta, stream);
+  }
+  launch_triplet<P>(mode, h->variant, ta, stream);
 }
 
 // The stored-Jacobian form applies to the FP64 and FP32 handles, and to
@@ -755,7 +777,7 @@ template <int P>
 nnp_status pair_mask_buffer(nnp_handle* h, int64_t n, TripArgs<P>& ta) {
   h->fwd_pm = nullptr;
   h->fwd_pm_stride = 0;
-  if (ta.wpc != 1 || !h->pair_masks || h->arena_on || h->lcap < PAIR_MASK_MIN_NEIGHBORS) return NNP_OK;
+  if (ta.wpc != 1 || h->has_wide || !h->pair_masks || h->arena_on || h->lcap < PAIR_MASK_MIN_NEIGHBORS) return NNP_OK;
   const int blocks = (pair_step_bound(h->lcap, h->n_el) + 31) / 32;
   const size_t words = (size_t)n * blocks * WAVE;
   if (words * sizeof(unsigned) > PAIR_MASK_MAX_BYTES) return NNP_OK;
@@ -835,7 +857,7 @@ nnp_status evaluate(nnp_handle* h, Common& cm, Marks& mk, const FwdBufs<P>& b, i
     if (!flat && (st = pair_mask_buffer<P>(h, n, ta))) return st;
     ta.G = b.G;
     if (flat) launch_flat<P>(0, ta, stream);
-    else launch_triplet<P>(0, h->variant, ta, stream);
+    else launch_wave<P>(h, 0, ta, stream);
     mk.mark("sf");
     launch_fill<FAcc>(b.F_s, n * 3, FAcc(0), stream);
     launch_mlp<P>(ma, stream);
@@ -843,7 +865,7 @@ nnp_status evaluate(nnp_handle* h, Common& cm, Marks& mk, const FwdBufs<P>& b, i
     ta.C = b.C;
     ta.F = b.F_s;
     if (flat) launch_flat<P>(1, ta, stream);
-    else launch_triplet<P>(1, h->variant, ta, stream);
+    else launch_wave<P>(h, 1, ta, stream);
     mk.mark("force");
   }
   const bool keep = remember || store;
@@ -1070,7 +1092,7 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
       if (!flat && (st = pair_mask_buffer<P>(h, n, ta))) return st;
       ta.G = G;
       if (flat) launch_flat<P>(0, ta, stream);
-      else launch_triplet<P>(0, h->variant, ta, stream);
+      else launch_wave<P>(h, 0, ta, stream);
       mk.mark("sf");
     }
     if ((st = fwd_remember<IO>(h, cm, pos, types, stream))) return st;
@@ -1101,7 +1123,7 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
     ta.delta = delta;
     ta.V = V;
     if (flat) launch_flat<P>(2, ta, stream);
-    else launch_triplet<P>(2, h->variant, ta, stream);
+    else launch_wave<P>(h, 2, ta, stream);
   }
   mk.mark("jvp");
   launch_gather_struct_grad(n, cm.bin.perm, cm.d_soff, n_struct, dL_dE, gE_atom, stream);
@@ -1232,7 +1254,7 @@ nnp_status build_table(nnp_handle* h, int n_el, int n_sf, const nnp_sf* sf, cons
   t.n_el = n_el;
   for (int e = 0; e < MAX_EL; ++e)
     for (int c = 0; c < MAX_CLS; ++c)
-      for (int b = 0; b < 12 * MAX_NE; ++b) t.qn_out[e][c][b] = -1;
+      for (int b = 0; b < 12 * MAX_NE; ++b) t.qn_out[e][c][b] = t.qw_out[e][c][b] = -1;
   h->rc = 0.0;
   std::vector<std::vector<double>> etas(n_el);
   std::vector<int> count(n_el, 0);
@@ -1289,11 +1311,16 @@ nnp_status build_table(nnp_handle* h, int n_el, int n_sf, const nnp_sf* sf, cons
           return fail(nullptr, NNP_E_ARG, at + "duplicate angular SF (same class, eta, zeta and lambda)");
         t.qn_out[e][cls][qb * MAX_NE + ei] = k;
         t.qn_pre[e][cls][qb * MAX_NE + ei] = std::pow(2.0, 1.0 - d.zeta);
-        qn_mask |= qn_bit(qb, ei);
       } else {
         t.ang_wide[e][cls][q] = 1;
         h->has_wide = true;
+        // a wide SF given twice is accepted, but has no place in the map
+        if (t.qw_out[e][cls][qb * MAX_NE + ei] >= 0) h->wide_flat = true;
+        t.qw_out[e][cls][qb * MAX_NE + ei] = k;
+        t.qw_pre[e][cls][qb * MAX_NE + ei] = std::pow(2.0, 1.0 - d.zeta);
       }
+      qn_mask |= qn_bit(qb, ei);
+      ++t.ang_kind[e][cls][d.kind == 3 ? 0 : 1];
       t.ang_bit[e][cls][q] = qb * MAX_NE + ei;
       t.ang_pre[e][cls][q] = std::pow(2.0, 1.0 - d.zeta);
       t.ang_out[e][cls][q] = k;

@@ -91,6 +91,10 @@ struct DevTab {
   // the same as a map from (q, n) to the one SF of the class using it (-1: none)
   int qn_out[MAX_EL][MAX_CLS][12 * MAX_NE];
   T qn_pre[MAX_EL][MAX_CLS][12 * MAX_NE];
+  // and of the wide functions; ang_kind: how many SFs of the class are narrow, wide
+  int qw_out[MAX_EL][MAX_CLS][12 * MAX_NE];
+  T qw_pre[MAX_EL][MAX_CLS][12 * MAX_NE];
+  int ang_kind[MAX_EL][MAX_CLS][2];
   // centring / scaling of the network inputs (applied in FP64 to the sums)
   double shift_d[MAX_EL][MAX_SF];
   double inv_scale_d[MAX_EL][MAX_SF];

@@ -1,7 +1,9 @@
 // Flat parallelism: one thread per centre atom, the paper's "flat" level
 // (threads over atoms only, Sec. 4.3), kept to compare the levels of
-// parallelism, and the path of tables with wide angular functions G9 (the
-// narrow function without its r_jk factor and cutoff: every pair counts).  Every lane is a centre and walks its own neighbours and
+// parallelism, for atoms whose neighbours exceed the LDS of the wave levels, and
+// for the wide angular functions G9 of the BF16 form (the narrow function
+// without its r_jk factor and cutoff: every pair counts).  Every lane is a
+// centre and walks its own neighbours and
 // pairs; a wave per centre (k_triplet) was measured faster on both workloads,
 // short neighbour rows included, because here each lane reads its own row
 // (64 rows per load instruction) and the pair loop diverges.

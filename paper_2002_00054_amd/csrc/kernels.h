@@ -106,7 +106,11 @@ __host__ __device__ constexpr int pair_step_bound(int m, int n_el) {
 }
 
 template <int P>
-void launch_triplet(int mode, int ne, const TripArgs<P>& a, hipStream_t stream);
+void launch_triplet(int mode, int variant, const TripArgs<P>& a, hipStream_t stream);
+// The same for tables with wide angular functions (one wave per centre, padded
+// rows, no pair-test masks).
+template <int P>
+void launch_triplet_wide(int mode, int variant, const TripArgs<P>& a, hipStream_t stream);
 // One thread per centre (mode 0: SF, 1: force, 2: force-adjoint product).
 template <int P>
 void launch_flat(int mode, const TripArgs<P>& a, hipStream_t stream);
