@@ -80,6 +80,8 @@ struct nnp_handle {
   size_t h_stage_bytes = 0;
   int* h_flags = nullptr;               // pinned [4]
   double* h_energy = nullptr;           // pinned [1]
+  int* h_flags_dev = nullptr;           // their device addresses
+  double* h_energy_dev = nullptr;
   // profiling
   bool prof = false;
   std::vector<const char*> t_names;
@@ -459,7 +461,10 @@ nnp_status prepare(nnp_handle* h, Common& cm, const IO* pos, const int32_t* type
     std::memcpy(hs + o_chi, B.chunk_hi.data(), nch * sizeof(int64_t));
   }
   std::memcpy(hs + o_sc, B.struct_chunk.data(), nsc * sizeof(int));
-  NNP_HIP(h, hipMemcpyAsync(d_desc, hs, bytes, hipMemcpyHostToDevice, stream));
+  // a short description goes with the first kernel's arguments (bin sort); a
+  // call that keeps the sorted order has no such kernel
+  const bool with_sort = sort && bytes <= DESC_BLOB_BYTES;
+  if (!with_sort) NNP_HIP(h, hipMemcpyAsync(d_desc, hs, bytes, hipMemcpyHostToDevice, stream));
   cm.d_st = reinterpret_cast<DevStruct*>(d_desc + o_st);
   cm.d_soff = reinterpret_cast<int64_t*>(d_desc + o_soff);
   cm.d_clo = reinterpret_cast<int64_t*>(d_desc + o_clo);
@@ -467,6 +472,10 @@ nnp_status prepare(nnp_handle* h, Common& cm, const IO* pos, const int32_t* type
   cm.d_sc = reinterpret_cast<int*>(d_desc + o_sc);
 
   BinArgs& a = cm.bin;
+  a.desc = reinterpret_cast<int*>(d_desc);
+  a.desc_host = with_sort ? hs : nullptr;
+  a.desc_bytes = bytes;
+  a.host_flags = h->h_flags_dev;
   a.n = n;
   a.types = types;
   a.st = cm.d_st;
@@ -483,13 +492,12 @@ nnp_status prepare(nnp_handle* h, Common& cm, const IO* pos, const int32_t* type
   if ((st = ensure_t(h, "perm_raw", std::max<int64_t>(n, 1), &a.perm_raw))) return st;
   if ((st = ensure_t(h, "pos4", std::max<int64_t>(n, 1), &a.pos4))) return st;
   if ((st = ensure_t(h, "eoff", MAX_EL + 1, &a.eoff))) return st;
-  if ((st = ensure_t(h, "flags", 4, &a.flags))) return st;
+  if ((st = ensure_t(h, "flags", N_FLAGS, &a.flags))) return st;
   if (!sort) return NNP_OK;
   h->fwd_valid = false;  // the sorted order, neighbour list, G~ and J store are about to change
   h->fwd_pm = nullptr;   // and so are the pair-test masks
   h->fwd_pm_stride = 0;
   h->skin_ok = false;    // and the Verlet-skin list with them
-  launch_fill_int(a.flags, 4, 0, stream);
   launch_bin_sort<IO>(a, pos, stream);
   return NNP_OK;
 }
@@ -521,14 +529,16 @@ nnp_status bind_neighbors(nnp_handle* h, Common& cm, int layout = NNP_LIST_PADDE
 // The neighbour build in the given layout.  The compact layout counts first,
 // scans the row lengths and reads the total back (a host wait) to size the
 // list, then writes it; its rows never overflow.
+// Leaves the flags in h_flags once the stream has been waited for.  first: the
+// flags are still as the sort left them.
 template <class T>
-nnp_status build_neighbors(nnp_handle* h, Common& cm, hipStream_t stream, int layout = NNP_LIST_PADDED) {
+nnp_status build_neighbors(nnp_handle* h, Common& cm, hipStream_t stream, bool first, int layout = NNP_LIST_PADDED) {
   using E = typename Vec4<T>::type;
   nnp_status st;
   const int64_t n = std::max<int64_t>(cm.B.n, 1);
   int* cmax = nullptr;
   if ((st = ensure_t(h, "cmax", std::max(cm.B.total_cells, 1), &cmax))) return st;
-  launch_fill_int(cm.bin.flags + 1, 2, 0, stream);
+  if (!first) launch_fill_int(cm.bin.flags + 1, 2, 0, stream);
   if (layout == NNP_LIST_COMPACT) {
     int *len, *tmp, *part, *roff;
     int4* nnb;
@@ -582,12 +592,13 @@ TripArgs<P> trip_args(nnp_handle* h, Common& cm) {
 // capacity overflowed (cap has been grown: rebuild), 0 if all is well (lcap
 // then bounds every atom's count), <0 on error.
 int check_flags(nnp_handle* h, hipStream_t stream, Common& cm, nnp_status* st) {
-  hipError_t e = hipMemcpyAsync(h->h_flags, cm.bin.flags, 4 * sizeof(int), hipMemcpyDeviceToHost, stream);
+  hipError_t e = hipGetLastError();  // a launch that failed wrote no flags
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) {
-    *st = fail(h, NNP_E_HIP, std::string("readback: ") + hipGetErrorString(e));
+    *st = fail(h, NNP_E_HIP, std::string("neighbour build: ") + hipGetErrorString(e));
     return -1;
   }
+  if (cm.B.n == 0) std::memset(h->h_flags, 0, 4 * sizeof(int));  // no build was launched
   if (h->h_flags[0] & 1) {
     *st = fail(h, NNP_E_TYPE, "atom type outside [0, n_el)");
     return -1;
@@ -724,10 +735,7 @@ nnp_status fwd_remember(nnp_handle* h, const Common& cm, const IO* pos, const in
   nnp_status st;
   if ((st = ensure_t(h, "jpos", (size_t)std::max<int64_t>(n, 1) * 3, &sp))) return st;
   if ((st = ensure_t(h, "jtypes", (size_t)std::max<int64_t>(n, 1), &stp))) return st;
-  if (n > 0) {
-    NNP_HIP(h, hipMemcpyAsync(sp, pos, (size_t)n * 3 * sizeof(IO), hipMemcpyDeviceToDevice, stream));
-    NNP_HIP(h, hipMemcpyAsync(stp, types, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToDevice, stream));
-  }
+  launch_copy_inputs<IO>(n, pos, types, sp, stp, stream);
   h->fwd_offs.assign(cm.B.soff.begin(), cm.B.soff.end());
   h->fwd_boxes.clear();
   for (const auto& d : cm.B.st) h->fwd_boxes.insert(h->fwd_boxes.end(), d.L, d.L + 3);
@@ -832,6 +840,7 @@ nnp_status evaluate(nnp_handle* h, Common& cm, Marks& mk, const FwdBufs<P>& b, i
   ma.G = b.G;
   ma.C = b.C;
   ma.Ei = b.Ei_s;
+  ma.F = b.F_s;  // cleared by the network pass
   ma.nets = reinterpret_cast<const T*>(h->d_nets);
   ma.tab = ta.tab;
   const bool store = use_store<P>(h);
@@ -842,7 +851,6 @@ nnp_status evaluate(nnp_handle* h, Common& cm, Marks& mk, const FwdBufs<P>& b, i
       ja.G = b.G;
       launch_jac<P>(ja, stream);
       mk.mark("sf");
-      launch_fill<FAcc>(b.F_s, n * 3, FAcc(0), stream);
       launch_mlp<P>(ma, stream);
       mk.mark("mlp");
       ja.C = b.C;
@@ -859,7 +867,6 @@ nnp_status evaluate(nnp_handle* h, Common& cm, Marks& mk, const FwdBufs<P>& b, i
     if (flat) launch_flat<P>(0, ta, stream);
     else launch_wave<P>(h, 0, ta, stream);
     mk.mark("sf");
-    launch_fill<FAcc>(b.F_s, n * 3, FAcc(0), stream);
     launch_mlp<P>(ma, stream);
     mk.mark("mlp");
     ta.C = b.C;
@@ -872,12 +879,10 @@ nnp_status evaluate(nnp_handle* h, Common& cm, Marks& mk, const FwdBufs<P>& b, i
   if (keep && (st = fwd_remember<IO>(h, cm, pos, types, stream))) return st;
   launch_unpermute<IO, FAcc>(n, cm.bin.perm, b.Ei_s, b.F_s, b.Ei_o, reinterpret_cast<IO*>(ei_v),
                              reinterpret_cast<IO*>(f_v), stream);
-  launch_energy(b.Ei_o, cm.d_clo, cm.d_chi, (int)cm.B.chunk_lo.size(), cm.d_sc, n_struct, b.partial, b.energies,
-                stream);
-  if (energies_dev)
-    NNP_HIP(h, hipMemcpyAsync(energies_dev, b.energies, n_struct * sizeof(double), hipMemcpyDeviceToDevice, stream));
-  if (energy_host)
-    NNP_HIP(h, hipMemcpyAsync(h->h_energy, b.energies, sizeof(double), hipMemcpyDeviceToHost, stream));
+  bool one_chunk_each = true;
+  for (int s = 0; s < n_struct; ++s) one_chunk_each &= cm.B.struct_chunk[s + 1] == cm.B.struct_chunk[s] + 1;
+  launch_energy(b.Ei_o, cm.d_clo, cm.d_chi, (int)cm.B.chunk_lo.size(), cm.d_sc, n_struct, one_chunk_each, b.partial,
+                energies_dev ? energies_dev : b.energies, energy_host ? h->h_energy_dev : nullptr, stream);
   mk.mark("finish");
   if ((st = check_launch(h, "forward"))) return st;
   // Device outputs are ready in stream order; the host waits only for a
@@ -911,7 +916,7 @@ nnp_status forward(nnp_handle* h, int n_struct, const int64_t* offs, const void*
   if ((st = fwd_buffers<P>(h, cm, n_struct, bufs))) return st;
   int layout = list_layout<P>(h);
   for (int attempt = 0; attempt < 8; ++attempt) {
-    if ((st = build_neighbors<T>(h, cm, stream, layout))) return st;
+    if ((st = build_neighbors<T>(h, cm, stream, attempt == 0, layout))) return st;
     const int r = check_flags(h, stream, cm, &st);
     if (r < 0) return st;
     if (r > 0) continue;  // capacity grew: rebuild the neighbour list
@@ -1061,7 +1066,7 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
   }
   int layout = list_layout<P>(h);
   for (int attempt = 0; attempt < 8 && !ready; ++attempt) {
-    if ((st = build_neighbors<T>(h, cm, stream, layout))) return st;
+    if ((st = build_neighbors<T>(h, cm, stream, attempt == 0, layout))) return st;
     const int r = check_flags(h, stream, cm, &st);
     if (r < 0) return st;
     if (r > 0) continue;  // capacity grew: rebuild the neighbour list
@@ -1436,6 +1441,9 @@ nnp_status nnp_create(int n_el, const char* const* elements, int n_sf, const nnp
     return bail(fail(h, NNP_E_NOMEM, "pinned flags"));
   if (hipHostMalloc((void**)&h->h_energy, sizeof(double), hipHostMallocDefault) != hipSuccess)
     return bail(fail(h, NNP_E_NOMEM, "pinned energy"));
+  if (hipHostGetDevicePointer((void**)&h->h_flags_dev, h->h_flags, 0) != hipSuccess ||
+      hipHostGetDevicePointer((void**)&h->h_energy_dev, h->h_energy, 0) != hipSuccess)
+    return bail(fail(h, NNP_E_HIP, "device address of the pinned flags"));
   if ((st = stage(h, 4096))) return bail(st);  // staging of one structure's batch description
   *out = h;
   return NNP_OK;
@@ -1468,7 +1476,8 @@ nnp_status nnp_count_work(nnp_handle* h, int64_t n_atoms, const void* pos, const
   if ((st = ensure_t(h, "counts", 8, &d_cnt))) return st;
   bool built = false;
   for (int attempt = 0; attempt < 8 && !built; ++attempt) {
-    st = h->prec == NNP_FP64 ? build_neighbors<double>(h, cm, s) : build_neighbors<float>(h, cm, s);
+    st = h->prec == NNP_FP64 ? build_neighbors<double>(h, cm, s, attempt == 0)
+                             : build_neighbors<float>(h, cm, s, attempt == 0);
     if (st) return st;
     const int r = check_flags(h, s, cm, &st);
     if (r < 0) return st;

@@ -111,28 +111,59 @@ __device__ inline double block_sum_256(double v) {
 }
 
 __global__ void __launch_bounds__(256) k_chunk_sum(const double* __restrict__ x, const int64_t* __restrict__ lo,
-                                                   const int64_t* __restrict__ hi, double* __restrict__ partial) {
+                                                   const int64_t* __restrict__ hi, double* __restrict__ partial,
+                                                   double* __restrict__ host) {
   const int c = blockIdx.x;
   double s = 0.0;
   for (int64_t i = lo[c] + threadIdx.x; i < hi[c]; i += 256) s += x[i];
   s = block_sum_256(s);
-  if (threadIdx.x == 0) partial[c] = s;
+  if (threadIdx.x == 0) {
+    partial[c] = s;
+    if (host && c == 0) __hip_atomic_store(host, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 __global__ void __launch_bounds__(256) k_struct_sum(const double* __restrict__ partial, const int* __restrict__ sc,
-                                                    double* __restrict__ out) {
+                                                    double* __restrict__ out, double* __restrict__ host) {
   const int b = blockIdx.x;
   double s = 0.0;
   for (int c = sc[b] + threadIdx.x; c < sc[b + 1]; c += 256) s += partial[c];
   s = block_sum_256(s);
-  if (threadIdx.x == 0) out[b] = s;
+  if (threadIdx.x == 0) {
+    out[b] = s;
+    if (host && b == 0) __hip_atomic_store(host, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
+template <class IO>
+__global__ void __launch_bounds__(256) k_copy_inputs(int64_t n, const IO* __restrict__ pos,
+                                                     const int32_t* __restrict__ types, IO* __restrict__ pos_out,
+                                                     int32_t* __restrict__ types_out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < 3 * n) pos_out[i] = pos[i];
+  if (i < n) types_out[i] = types[i];
+}
+
+template <class IO>
+void launch_copy_inputs(int64_t n, const IO* pos, const int32_t* types, IO* pos_out, int32_t* types_out,
+                        hipStream_t stream) {
+  if (n <= 0) return;
+  hipLaunchKernelGGL(k_copy_inputs<IO>, dim3((unsigned)((3 * n + 255) / 256)), dim3(256), 0, stream, n, pos, types,
+                     pos_out, types_out);
+}
+template void launch_copy_inputs<float>(int64_t, const float*, const int32_t*, float*, int32_t*, hipStream_t);
+template void launch_copy_inputs<double>(int64_t, const double*, const int32_t*, double*, int32_t*, hipStream_t);
+
 void launch_energy(const double* Ei_o, const int64_t* chunk_lo, const int64_t* chunk_hi, int nchunk,
-                   const int* struct_chunk, int n_struct, double* partial, double* energies, hipStream_t stream) {
+                   const int* struct_chunk, int n_struct, bool one_chunk_each, double* partial, double* energies,
+                   double* host, hipStream_t stream) {
+  if (one_chunk_each) {  // a chunk's sum is its structure's energy
+    hipLaunchKernelGGL(k_chunk_sum, dim3(nchunk), dim3(256), 0, stream, Ei_o, chunk_lo, chunk_hi, energies, host);
+    return;
+  }
   if (nchunk > 0)
-    hipLaunchKernelGGL(k_chunk_sum, dim3(nchunk), dim3(256), 0, stream, Ei_o, chunk_lo, chunk_hi, partial);
-  hipLaunchKernelGGL(k_struct_sum, dim3(n_struct), dim3(256), 0, stream, partial, struct_chunk, energies);
+    hipLaunchKernelGGL(k_chunk_sum, dim3(nchunk), dim3(256), 0, stream, Ei_o, chunk_lo, chunk_hi, partial, nullptr);
+  hipLaunchKernelGGL(k_struct_sum, dim3(n_struct), dim3(256), 0, stream, partial, struct_chunk, energies, host);
 }
 
 }  // namespace nnp

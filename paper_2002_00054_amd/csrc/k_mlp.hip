@@ -175,6 +175,8 @@ __global__ void __launch_bounds__(256) k_mlp_mfma(MlpArgs<P> a, int wpe) {
     pe += __shfl_xor(pe, 16, 64);
     pe += __shfl_xor(pe, 32, 64);
     if (g == 0 && valid) a.Ei[atom] = (IO)(pe + b3);
+    // the force pass's accumulator, cleared here (one launch fewer per call)
+    if (g < 3 && valid) a.F[g * a.n + atom] = typename Types<P>::FAcc(0);
     layer<P>(d, false, W2t, false, y);
 #pragma unroll
     for (int s = 0; s < 8; ++s) d[s] = y[s] * (T(1) - h1[s] * h1[s]);

@@ -24,10 +24,18 @@ struct BinArgs {
   double4* pos4;             // [n] sorted wrapped positions + ids
   int* eoff;                 // [n_el + 1] element offsets of the sorted order
   int* flags;                // [0] bit 0 bad type, bit 1 non-finite position, bit 2 skin exceeded;
-                             // [1] max neighbour count beyond cap, [2] max count, [3] inputs differ
+                             // [1] max neighbour count beyond cap, [2] max count, [3] inputs differ,
+                             // [4] workgroups of the neighbour build that are done
+  int* host_flags;           // pinned copy of [0..3], written at the end of the neighbour build
+  int* desc;                 // device block of the batch description (st, soff, ...)
+  const void* desc_host;     // its contents, if the sort is to write them (at most DESC_BLOB_BYTES), else null
+  size_t desc_bytes;
 };
+constexpr int N_FLAGS = 5;
+constexpr size_t DESC_BLOB_BYTES = 1024;
 
 void launch_fill_int(int* p, int64_t n, int v, hipStream_t stream);
+// Clears the flags, writes the batch description if it is given, and sorts.
 template <class TIn>
 void launch_bin_sort(const BinArgs& a, const TIn* pos, hipStream_t stream);
 // Neighbour rows of (dx, dy, dz, j) entries; cmax: [total_cells] scratch.
@@ -182,7 +190,7 @@ struct MlpArgs {
   IO* C;                     // [n][LD] dE/dG (raw G)
   IO* Ei;                    // [n] atomic energies (sorted)
   const T* nets;             // [n_el][NET_STRIDE] padded parameters
-  const uint16_t* bf;        // BF16 form: split weights (see k_mlp.hip), else null
+  typename Types<P>::FAcc* F;  // force accumulator [3][n], cleared here for the force pass
   const DevTab<T>* tab;
 };
 template <int P>
@@ -223,8 +231,15 @@ template <class IO>
 void launch_permute_rows3(int64_t n, const int* perm, const IO* in, IO* out, hipStream_t stream);
 void launch_gather_struct_grad(int64_t n, const int* perm, const int64_t* soff, int n_struct, const double* gE,
                                double* gE_atom, hipStream_t stream);
-// Deterministic energy sums: chunk partials then per-structure sums.
+// Deterministic energy sums: chunk partials then per-structure sums (the chunk
+// sums alone where every structure is one chunk).  host (may be null): pinned,
+// receives the first structure's energy.
 void launch_energy(const double* Ei_o, const int64_t* chunk_lo, const int64_t* chunk_hi, int nchunk,
-                   const int* struct_chunk, int n_struct, double* partial, double* energies, hipStream_t stream);
+                   const int* struct_chunk, int n_struct, bool one_chunk_each, double* partial, double* energies,
+                   double* host, hipStream_t stream);
+// Copies of the inputs of a batch forward.
+template <class IO>
+void launch_copy_inputs(int64_t n, const IO* pos, const int32_t* types, IO* pos_out, int32_t* types_out,
+                        hipStream_t stream);
 
 }  // namespace nnp
