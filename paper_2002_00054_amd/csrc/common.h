@@ -197,6 +197,20 @@ __device__ inline void wave_sum_many(const Acc (&x)[K], Acc* out, int lane) {
 }
 
 
+// Lets the passes after a neighbour build be launched before the host has seen
+// the build's flags: they do nothing where it failed, or where the rows
+// outgrew what the passes were launched with.  flags: the build's, 16-byte
+// aligned (null: the host has seen them).
+struct Gate {
+  const int* flags;
+  int cap, lcap;
+};
+__device__ inline bool gate_closed(const Gate& g) {
+  if (!g.flags) return false;
+  const int4 f = *reinterpret_cast<const int4*>(g.flags);
+  return ((f.x & 7) | f.w) != 0 || f.y > g.cap || f.z > g.lcap;
+}
+
 __device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Workgroup index remapped so that each XCD (workgroups are dealt round-robin

@@ -397,7 +397,8 @@ __device__ inline bool same_bits(double x, double y) { return __double_as_longlo
 
 template <class IO>
 __global__ void __launch_bounds__(256) k_same_inputs(int64_t n, const IO* pos, const IO* saved_pos,
-                                                     const int32_t* types, const int32_t* saved_types, int* flag) {
+                                                     const int32_t* types, const int32_t* saved_types, int* flag,
+                                                     int* host_flag) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   bool diff = false;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
@@ -406,7 +407,10 @@ __global__ void __launch_bounds__(256) k_same_inputs(int64_t n, const IO* pos, c
     diff |= !same_bits(pos[3 * i + 1], saved_pos[3 * i + 1]);
     diff |= !same_bits(pos[3 * i + 2], saved_pos[3 * i + 2]);
   }
-  if (diff) flag[0] = 1;
+  if (diff) {
+    flag[0] = 1;
+    __hip_atomic_store(host_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 int64_t wave_blocks(int64_t n) { return (n + 3) / 4; }
@@ -445,11 +449,11 @@ void launch_jac_jvp(const JacArgs<P>& a, hipStream_t stream) {
 
 template <class IO>
 void launch_same_inputs(int64_t n, const IO* pos, const IO* saved_pos, const int32_t* types,
-                        const int32_t* saved_types, int* flag, hipStream_t stream) {
+                        const int32_t* saved_types, int* flag, int* host_flag, hipStream_t stream) {
   if (n == 0) return;
   const int64_t blocks = std::min<int64_t>((n + 255) / 256, 4096);
   hipLaunchKernelGGL(k_same_inputs<IO>, dim3((unsigned)blocks), dim3(256), 0, stream, n, pos, saved_pos, types,
-                     saved_types, flag);
+                     saved_types, flag, host_flag);
 }
 
 template size_t jac_lds_bytes<P_FP64>(int);
@@ -461,8 +465,8 @@ template void launch_jac_force<P_FP32>(const JacArgs<P_FP32>&, hipStream_t);
 template void launch_jac_jvp<P_FP64>(const JacArgs<P_FP64>&, hipStream_t);
 template void launch_jac_jvp<P_FP32>(const JacArgs<P_FP32>&, hipStream_t);
 template void launch_same_inputs<float>(int64_t, const float*, const float*, const int32_t*, const int32_t*, int*,
-                                        hipStream_t);
+                                        int*, hipStream_t);
 template void launch_same_inputs<double>(int64_t, const double*, const double*, const int32_t*, const int32_t*,
-                                         int*, hipStream_t);
+                                         int*, int*, hipStream_t);
 
 }  // namespace nnp

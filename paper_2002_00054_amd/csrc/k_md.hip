@@ -18,7 +18,8 @@ __device__ inline int clamp_type(int t) { return t < 0 ? 0 : (t >= MAX_EL ? MAX_
 
 template <class IO>
 __global__ void __launch_bounds__(MD_THREADS) k_kick_drift(int64_t n, IO* pos, IO* vel, const IO* F,
-                                                           const int32_t* types, MdArgs m) {
+                                                           const int32_t* types, MdArgs m, int* flags) {
+  if (flags && blockIdx.x == 0 && threadIdx.x < 4) flags[threadIdx.x] = 0;
   const int64_t stride = (int64_t)gridDim.x * MD_THREADS;
   for (int64_t i = (int64_t)blockIdx.x * MD_THREADS + threadIdx.x; i < n; i += stride) {
     const double h = m.half_kick[clamp_type(types[i])];
@@ -76,10 +77,11 @@ __global__ void k_ke_total(const double* partial, int nb, double conv, double* o
 int md_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>((n + MD_THREADS - 1) / MD_THREADS, 1024)); }
 
 template <class IO>
-void launch_kick_drift(int64_t n, IO* pos, IO* vel, const IO* F, const int32_t* types, const MdArgs& m,
+void launch_kick_drift(int64_t n, IO* pos, IO* vel, const IO* F, const int32_t* types, const MdArgs& m, int* flags,
                        hipStream_t stream) {
   if (n == 0) return;
-  hipLaunchKernelGGL(k_kick_drift<IO>, dim3(md_blocks(n)), dim3(MD_THREADS), 0, stream, n, pos, vel, F, types, m);
+  hipLaunchKernelGGL(k_kick_drift<IO>, dim3(md_blocks(n)), dim3(MD_THREADS), 0, stream, n, pos, vel, F, types, m,
+                     flags);
 }
 
 template <class IO>
@@ -92,9 +94,9 @@ void launch_kick_ke(int64_t n, IO* vel, const IO* F, const int32_t* types, const
   hipLaunchKernelGGL(k_ke_total, dim3(1), dim3(64), 0, stream, partial, n > 0 ? nb : 0, m.ke_conv, ke_out);
 }
 
-template void launch_kick_drift<float>(int64_t, float*, float*, const float*, const int32_t*, const MdArgs&,
+template void launch_kick_drift<float>(int64_t, float*, float*, const float*, const int32_t*, const MdArgs&, int*,
                                        hipStream_t);
-template void launch_kick_drift<double>(int64_t, double*, double*, const double*, const int32_t*, const MdArgs&,
+template void launch_kick_drift<double>(int64_t, double*, double*, const double*, const int32_t*, const MdArgs&, int*,
                                         hipStream_t);
 template void launch_kick_ke<float>(int64_t, float*, const float*, const int32_t*, const MdArgs&, bool, double*,
                                     double*, hipStream_t);

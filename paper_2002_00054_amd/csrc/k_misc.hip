@@ -24,9 +24,9 @@ void launch_fill_int(int* p, int64_t n, int v, hipStream_t stream) { launch_fill
 template <class IO, class FAcc>
 __global__ void __launch_bounds__(256) k_unpermute(int64_t n, const int* __restrict__ perm, const IO* __restrict__ Ei_s,
                                                    const FAcc* __restrict__ F_s, double* __restrict__ Ei_o,
-                                                   IO* __restrict__ Ei_out, IO* __restrict__ F_out) {
+                                                   IO* __restrict__ Ei_out, IO* __restrict__ F_out, Gate gate) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
+  if (s >= n || gate_closed(gate)) return;
   const int64_t i = perm[s];
   const IO e = Ei_s[s];
   Ei_o[i] = (double)e;
@@ -40,17 +40,17 @@ __global__ void __launch_bounds__(256) k_unpermute(int64_t n, const int* __restr
 
 template <class IO, class FAcc>
 void launch_unpermute(int64_t n, const int* perm, const IO* Ei_s, const FAcc* F_s, double* Ei_o, IO* Ei_out,
-                      IO* F_out, hipStream_t stream) {
+                      IO* F_out, const Gate& gate, hipStream_t stream) {
   if (n <= 0) return;
   hipLaunchKernelGGL((k_unpermute<IO, FAcc>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, n, perm, Ei_s,
-                     F_s, Ei_o, Ei_out, F_out);
+                     F_s, Ei_o, Ei_out, F_out, gate);
 }
 template void launch_unpermute<double, double>(int64_t, const int*, const double*, const double*, double*, double*,
-                                               double*, hipStream_t);
+                                               double*, const Gate&, hipStream_t);
 template void launch_unpermute<float, float>(int64_t, const int*, const float*, const float*, double*, float*, float*,
-                                             hipStream_t);
+                                             const Gate&, hipStream_t);
 template void launch_unpermute<float, double>(int64_t, const int*, const float*, const double*, double*, float*,
-                                              float*, hipStream_t);
+                                              float*, const Gate&, hipStream_t);
 
 // out[s] = in[perm[s]] for rows of 3 (caller order -> sorted order).
 template <class IO>
@@ -112,7 +112,8 @@ __device__ inline double block_sum_256(double v) {
 
 __global__ void __launch_bounds__(256) k_chunk_sum(const double* __restrict__ x, const int64_t* __restrict__ lo,
                                                    const int64_t* __restrict__ hi, double* __restrict__ partial,
-                                                   double* __restrict__ host) {
+                                                   double* __restrict__ host, Gate gate) {
+  if (gate_closed(gate)) return;
   const int c = blockIdx.x;
   double s = 0.0;
   for (int64_t i = lo[c] + threadIdx.x; i < hi[c]; i += 256) s += x[i];
@@ -124,7 +125,8 @@ __global__ void __launch_bounds__(256) k_chunk_sum(const double* __restrict__ x,
 }
 
 __global__ void __launch_bounds__(256) k_struct_sum(const double* __restrict__ partial, const int* __restrict__ sc,
-                                                    double* __restrict__ out, double* __restrict__ host) {
+                                                    double* __restrict__ out, double* __restrict__ host, Gate gate) {
+  if (gate_closed(gate)) return;
   const int b = blockIdx.x;
   double s = 0.0;
   for (int c = sc[b] + threadIdx.x; c < sc[b + 1]; c += 256) s += partial[c];
@@ -156,14 +158,17 @@ template void launch_copy_inputs<double>(int64_t, const double*, const int32_t*,
 
 void launch_energy(const double* Ei_o, const int64_t* chunk_lo, const int64_t* chunk_hi, int nchunk,
                    const int* struct_chunk, int n_struct, bool one_chunk_each, double* partial, double* energies,
-                   double* host, hipStream_t stream) {
+                   double* host, const Gate& gate, hipStream_t stream) {
   if (one_chunk_each) {  // a chunk's sum is its structure's energy
-    hipLaunchKernelGGL(k_chunk_sum, dim3(nchunk), dim3(256), 0, stream, Ei_o, chunk_lo, chunk_hi, energies, host);
+    hipLaunchKernelGGL(k_chunk_sum, dim3(nchunk), dim3(256), 0, stream, Ei_o, chunk_lo, chunk_hi, energies, host,
+                       gate);
     return;
   }
   if (nchunk > 0)
-    hipLaunchKernelGGL(k_chunk_sum, dim3(nchunk), dim3(256), 0, stream, Ei_o, chunk_lo, chunk_hi, partial, nullptr);
-  hipLaunchKernelGGL(k_struct_sum, dim3(n_struct), dim3(256), 0, stream, partial, struct_chunk, energies, host);
+    hipLaunchKernelGGL(k_chunk_sum, dim3(nchunk), dim3(256), 0, stream, Ei_o, chunk_lo, chunk_hi, partial, nullptr,
+                       gate);
+  hipLaunchKernelGGL(k_struct_sum, dim3(n_struct), dim3(256), 0, stream, partial, struct_chunk, energies, host,
+                     gate);
 }
 
 }  // namespace nnp

@@ -121,7 +121,23 @@ __device__ inline void layer(const T (&in)[8], bool in_row, WF w, bool first, T 
   else layer_k4<T>(in, in_row, w, out);
 }
 
-// Grid: n_el x wpe workgroups of 4 waves; workgroup (e, b) serves element e,
+// flags[2] = the largest of itself and cmax[0 .. ncells); the host's copy of flags[0..3].
+__device__ inline void report_flags(int* flags, const int* cmax, int ncells, int* host_flags) {
+  __shared__ int red[4];
+  int m = 0;
+  for (int i = threadIdx.x; i < ncells; i += 256) m = max(m, cmax[i]);
+  for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  m = max(max(flags[2], max(red[0], red[1])), max(red[2], red[3]));
+  flags[2] = m;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    __hip_atomic_store(&host_flags[i], i == 2 ? m : flags[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Grid: n_el x wpe workgroups of 4 waves (and one that reports the flags); workgroup (e, b) serves element e,
 // its waves striding over that element's 16-atom tiles.  The element's
 // padded weights are staged in LDS once per workgroup.
 template <int P>
@@ -132,7 +148,11 @@ __global__ void __launch_bounds__(256) k_mlp_mfma(MlpArgs<P> a, int wpe) {
   __shared__ T isc[HID];
   const int e = uniform(blockIdx.x / wpe);
   const int b = blockIdx.x % wpe;
-  if (e >= a.n_el) return;
+  if (e >= a.n_el) {  // the extra workgroup (MlpArgs::host_flags)
+    report_flags(a.flags, a.cmax, a.ncells, a.host_flags);
+    return;
+  }
+  if (gate_closed(a.gate)) return;
   const T* __restrict__ src = a.nets + (size_t)e * NET_STRIDE;
   for (int i = threadIdx.x; i < NET_STRIDE; i += 256) W[i] = src[i];
   if (threadIdx.x < HID) isc[threadIdx.x] = threadIdx.x < MAX_SF ? (T)a.tab->inv_scale_d[e][threadIdx.x] : T(0);
@@ -196,7 +216,8 @@ void launch_mlp(const MlpArgs<P>& a, hipStream_t stream) {
   if (a.n == 0) return;
   int wpe = (int)std::min<int64_t>(512, (a.n + 63) / 64);
   if (wpe < 1) wpe = 1;
-  hipLaunchKernelGGL(k_mlp_mfma<P>, dim3((unsigned)(a.n_el * wpe)), dim3(256), 0, stream, a, wpe);
+  hipLaunchKernelGGL(k_mlp_mfma<P>, dim3((unsigned)(a.n_el * wpe + (a.host_flags ? 1 : 0))), dim3(256), 0,
+                     stream, a, wpe);
 }
 
 // ------------------------------------------------------------ weight gradient
@@ -217,6 +238,7 @@ __global__ void __launch_bounds__(256) k_wgrad_atoms(WGradArgs<P> a) {
   using T = typename Types<P>::T;
   using V4 = typename Vec4<T>::type;
   constexpr int ATOMS = 256 / HID;  // atoms per block
+  if (gate_closed(a.gate)) return;
   int e;
   int64_t r0, r1;
   if (!element_tile(blockIdx.x, ATOMS, a.n_el, a.eoff, e, r0, r1)) return;
@@ -299,7 +321,9 @@ template <> struct PairOf<double> { using type = double2; };
 // index t, thread 32 owns b3, and threads 33-63 write the padding (zero).
 template <class T>
 __global__ void __launch_bounds__(256) k_wgrad_chunks(const int* __restrict__ eoff, int chunk, int nch,
-                                                      const T* __restrict__ vec, double* __restrict__ partial) {
+                                                      const T* __restrict__ vec, double* __restrict__ partial,
+                                                      Gate gate) {
+  if (gate_closed(gate)) return;
   using T2 = typename PairOf<T>::type;
   static_assert(HID == 32 && NET_STRIDE == OFF_B3 + HID, "tile map covers the padded layout exactly");
   const int e = blockIdx.y;
@@ -380,9 +404,9 @@ __global__ void __launch_bounds__(256) k_wgrad_final(int nch, const double* __re
 
 // Padded gradient -> caller's flat parameter layout.
 __global__ void __launch_bounds__(256) k_unpad(int64_t np, const int* __restrict__ map, const double* __restrict__ padded,
-                                               double* __restrict__ flat) {
+                                               double* __restrict__ flat, Gate gate) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < np) flat[i] = padded[map[i]];
+  if (i < np && !gate_closed(gate)) flat[i] = padded[map[i]];
 }
 
 template <int P>
@@ -393,11 +417,11 @@ void launch_wgrad(const WGradArgs<P>& a, hipStream_t stream) {
     hipLaunchKernelGGL(k_wgrad_atoms<P>, dim3(g), dim3(256), 0, stream, a);
   }
   hipLaunchKernelGGL(k_wgrad_chunks<T>, dim3((unsigned)a.nch, a.n_el), dim3(256), 0, stream, a.eoff, a.chunk, a.nch,
-                     (const T*)a.vec, a.partial);
+                     (const T*)a.vec, a.partial, a.gate);
   hipLaunchKernelGGL(k_wgrad_final, dim3((NET_STRIDE + 31) / 32, a.n_el), dim3(256), 0, stream, a.nch, a.partial,
                      a.padded);
   hipLaunchKernelGGL(k_unpad, dim3((unsigned)((a.n_params + 255) / 256)), dim3(256), 0, stream, a.n_params, a.flatmap,
-                     a.padded, a.out);
+                     a.padded, a.out, a.gate);
 }
 
 template void launch_mlp<P_FP64>(const MlpArgs<P_FP64>&, hipStream_t);

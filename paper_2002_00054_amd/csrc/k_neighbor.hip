@@ -807,11 +807,11 @@ template <class E>
 void launch_neighbors_as(const BinArgs& a, double rc, int cap, E* nbr, int4* nnb, int* cmax, hipStream_t stream,
                          const int* roff = nullptr) {
   if (a.n == 0) return;
-  const bool small = a.total_cells <= DIRECT_MAX_CELLS;
+  const bool small = a.host_flags && a.total_cells <= DIRECT_MAX_CELLS;
   hipLaunchKernelGGL(k_neighbors<E>, dim3((unsigned)a.total_cells), dim3(256), 0, stream, a.pos4, a.st, a.n_struct,
                      a.start, a.n_el, a.total_cells, rc * rc, cap, nbr, nnb, a.flags, cmax, roff,
                      small ? a.host_flags : nullptr);
-  if (small) return;
+  if (small || !a.host_flags) return;
   hipLaunchKernelGGL(k_max_count, dim3((unsigned)std::max(1, (a.total_cells + MAXC_PER - 1) / MAXC_PER)), dim3(256), 0,
                      stream, a.total_cells, cmax, a.flags, a.host_flags);
 }

@@ -26,7 +26,8 @@ struct BinArgs {
   int* flags;                // [0] bit 0 bad type, bit 1 non-finite position, bit 2 skin exceeded;
                              // [1] max neighbour count beyond cap, [2] max count, [3] inputs differ,
                              // [4] workgroups of the neighbour build that are done
-  int* host_flags;           // pinned copy of [0..3], written at the end of the neighbour build
+  int* host_flags;           // pinned copy of [0..3], written at the end of the neighbour build;
+                             // null: the build leaves its counts in cmax for the network pass
   int* desc;                 // device block of the batch description (st, soff, ...)
   const void* desc_host;     // its contents, if the sort is to write them (at most DESC_BLOB_BYTES), else null
   size_t desc_bytes;
@@ -101,6 +102,7 @@ struct TripArgs {
   unsigned* pm;
   int pm_stride;
   int poly;                  // FP64: the table's X_n polynomials are accurate (DevTab::xpoly)
+  Gate gate;
 };
 
 // Most steps the one-wave pair walk can take for a centre with m neighbours
@@ -160,7 +162,7 @@ template <int P>
 void launch_jac_jvp(const JacArgs<P>& a, hipStream_t stream);      // V from J and delta
 template <class IO>
 void launch_same_inputs(int64_t n, const IO* pos, const IO* saved_pos, const int32_t* types,
-                        const int32_t* saved_types, int* flag, hipStream_t stream);
+                        const int32_t* saved_types, int* flag, int* host_flag, hipStream_t stream);
 
 // ------------------------------------------------------ velocity Verlet
 struct MdArgs {
@@ -172,8 +174,8 @@ struct MdArgs {
 };
 int md_blocks(int64_t n);    // blocks of the kinetic-energy partial sums
 template <class IO>
-void launch_kick_drift(int64_t n, IO* pos, IO* vel, const IO* F, const int32_t* types, const MdArgs& m,
-                       hipStream_t stream);
+void launch_kick_drift(int64_t n, IO* pos, IO* vel, const IO* F, const int32_t* types, const MdArgs& m, int* flags,
+                       hipStream_t stream);  // and flags[0..3] = 0 (flags may be null)
 template <class IO>
 void launch_kick_ke(int64_t n, IO* vel, const IO* F, const int32_t* types, const MdArgs& m, bool kick,
                     double* partial, double* ke_out, hipStream_t stream);
@@ -191,6 +193,13 @@ struct MlpArgs {
   IO* Ei;                    // [n] atomic energies (sorted)
   const T* nets;             // [n_el][NET_STRIDE] padded parameters
   typename Types<P>::FAcc* F;  // force accumulator [3][n], cleared here for the force pass
+  Gate gate;
+  // With host_flags, one more workgroup sets flags[2] to the largest of
+  // cmax[0 .. ncells) (and of itself) and copies flags[0..3] to the host.
+  int* host_flags;
+  int* flags;
+  const int* cmax;
+  int ncells;
   const DevTab<T>* tab;
 };
 template <int P>
@@ -217,6 +226,7 @@ struct WGradArgs {
   int64_t n_params;
   const int* flatmap;        // [n_params] flat index -> padded index
   double* out;               // [n_params] caller layout
+  Gate gate;
 };
 template <int P>
 void launch_wgrad(const WGradArgs<P>& a, hipStream_t stream);
@@ -226,7 +236,7 @@ template <class T>
 void launch_fill(T* p, int64_t n, T v, hipStream_t stream);
 template <class IO, class FAcc>
 void launch_unpermute(int64_t n, const int* perm, const IO* Ei_s, const FAcc* F_s, double* Ei_o, IO* Ei_out,
-                      IO* F_out, hipStream_t stream);
+                      IO* F_out, const Gate& gate, hipStream_t stream);
 template <class IO>
 void launch_permute_rows3(int64_t n, const int* perm, const IO* in, IO* out, hipStream_t stream);
 void launch_gather_struct_grad(int64_t n, const int* perm, const int64_t* soff, int n_struct, const double* gE,
@@ -236,7 +246,7 @@ void launch_gather_struct_grad(int64_t n, const int* perm, const int64_t* soff, 
 // receives the first structure's energy.
 void launch_energy(const double* Ei_o, const int64_t* chunk_lo, const int64_t* chunk_hi, int nchunk,
                    const int* struct_chunk, int n_struct, bool one_chunk_each, double* partial, double* energies,
-                   double* host, hipStream_t stream);
+                   double* host, const Gate& gate, hipStream_t stream);
 // Copies of the inputs of a batch forward.
 template <class IO>
 void launch_copy_inputs(int64_t n, const IO* pos, const int32_t* types, IO* pos_out, int32_t* types_out,
