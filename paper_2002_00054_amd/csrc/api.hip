@@ -598,8 +598,10 @@ TripArgs<P> trip_args(nnp_handle* h, Common& cm) {
 // Row capacity for the counts in h_flags: exact for this call's passes, and for
 // the next call's the same or, while the counts stay within one step of 8 below
 // it, the last one (counts of a running simulation move by a few).
-void set_lcap(nnp_handle* h) {
-  h->lcap = std::min(h->cap, (std::max(h->h_flags[2], 1) + 7) / 8 * 8);
+// Compact rows are not bounded by cap.
+void set_lcap(nnp_handle* h, int layout) {
+  h->lcap = (std::max(h->h_flags[2], 1) + 7) / 8 * 8;
+  if (layout != NNP_LIST_COMPACT) h->lcap = std::min(h->lcap, h->cap);
   if (h->lcap > h->lcap_next || h->lcap + 8 < h->lcap_next) h->lcap_next = h->lcap;
 }
 
@@ -630,7 +632,7 @@ int check_flags(nnp_handle* h, hipStream_t stream, Common& cm, nnp_status* st, b
     return 1;
   }
   const int was = ahead ? h->lcap : 0;
-  set_lcap(h);
+  set_lcap(h, cm.layout);
   if (!ahead) return 0;
   if (h->lcap > was) return 2;
   h->lcap = was;  // what this call's rows and masks are laid out for
@@ -1119,7 +1121,7 @@ nnp_status forward_skin(nnp_handle* h, int64_t n, const void* pos_v, const int32
       if (ahead) mk.restart();
       continue;  // the next round re-gathers (unchanged) and refreshes into the larger rows
     }
-    set_lcap(h);
+    set_lcap(h, cm.layout);
     if (ahead && h->lcap <= lcap) {
       h->lcap = lcap;
       return evaluated(h, mk, nullptr, false, false, stream);
