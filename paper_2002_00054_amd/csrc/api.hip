@@ -3,6 +3,7 @@
 // kernel sequence of one call on the caller's stream.
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -74,7 +75,9 @@ struct nnp_handle {
   std::map<std::string, nnp::DevBuf> ws;
   int cap = 0;                          // neighbour slots per atom
   int lcap = 0;                         // at least the most neighbours of any atom in the last build, rounded up
-  int lcap_next = 0;                    // capacity to launch the next call's passes with (0: none yet)
+  int lcap_next = 0;                    // capacity to launch the next call's passes with (0: none yet),
+  int lcap_lower = 0;                   // calls since one needed it, and the most that these needed
+  int lcap_recent = 0;
   hipEvent_t reported = nullptr;        // a call that launches ahead of its flags waits for this
   int cap_override = 0;
   // pinned staging for small uploads / readbacks
@@ -483,6 +486,7 @@ nnp_status prepare(nnp_handle* h, Common& cm, const IO* pos, const int32_t* type
   a.desc_host = with_sort ? hs : nullptr;
   a.desc_bytes = bytes;
   a.host_flags = h->h_flags_dev;
+  a.clip = INT_MAX;
   a.n = n;
   a.types = types;
   a.st = cm.d_st;
@@ -508,6 +512,9 @@ nnp_status prepare(nnp_handle* h, Common& cm, const IO* pos, const int32_t* type
   launch_bin_sort<IO>(a, pos, stream);
   return NNP_OK;
 }
+
+// Workgroups of the neighbour build, each with a count in cmax.
+int count_blocks(const Batch& B) { return std::max(B.total_cells, 1) * neighbor_split(B.n, std::max(B.total_cells, 1)); }
 
 // Binds the neighbour list of the given layout that the workspace holds
 // (padded entries, index entries, or compact entries with their offsets).
@@ -544,7 +551,7 @@ nnp_status build_neighbors(nnp_handle* h, Common& cm, hipStream_t stream, bool f
   nnp_status st;
   const int64_t n = std::max<int64_t>(cm.B.n, 1);
   int* cmax = nullptr;
-  if ((st = ensure_t(h, "cmax", std::max(cm.B.total_cells, 1), &cmax))) return st;
+  if ((st = ensure_t(h, "cmax", count_blocks(cm.B), &cmax))) return st;
   if (!first) launch_fill_int(cm.bin.flags + 1, 2, 0, stream);
   if (layout == NNP_LIST_COMPACT) {
     int *len, *tmp, *part, *roff;
@@ -596,19 +603,27 @@ TripArgs<P> trip_args(nnp_handle* h, Common& cm) {
 }
 
 // Row capacity for the counts in h_flags: exact for this call's passes, and for
-// the next call's the same or, while the counts stay within one step of 8 below
-// it, the last one (counts of a running simulation move by a few).
-// Compact rows are not bounded by cap.
+// the next call's the most that one of the last calls needed (it shrinks after 16
+// calls that needed less).  Compact rows are not bounded by cap.
 void set_lcap(nnp_handle* h, int layout) {
   h->lcap = (std::max(h->h_flags[2], 1) + 7) / 8 * 8;
   if (layout != NNP_LIST_COMPACT) h->lcap = std::min(h->lcap, h->cap);
-  if (h->lcap > h->lcap_next || h->lcap + 8 < h->lcap_next) h->lcap_next = h->lcap;
+  if (h->lcap >= h->lcap_next) {
+    h->lcap_next = h->lcap;
+    h->lcap_lower = h->lcap_recent = 0;
+  } else {
+    h->lcap_recent = std::max(h->lcap_recent, h->lcap);
+    if (++h->lcap_lower == 16) {
+      h->lcap_next = h->lcap_recent;
+      h->lcap_lower = h->lcap_recent = 0;
+    }
+  }
 }
 
 // Waits for the flags of a neighbour build; returns 1 if the neighbour
-// capacity overflowed (cap has been grown: rebuild), 0 if all is well (lcap
+// capacity overflowed (rebuild), 0 if all is well (lcap
 // then bounds every atom's count), <0 on error.  ahead: the passes are launched
-// already, with h->lcap; 2 if a row outgrew it (they did nothing: launch again).
+// already, with rows cut at h->lcap; 1 too if a row outgrew it.
 // event: wait for h->reported, not for the whole stream.
 int check_flags(nnp_handle* h, hipStream_t stream, Common& cm, nnp_status* st, bool ahead = false, bool event = false) {
   hipError_t e = hipGetLastError();  // a launch that failed wrote no flags
@@ -634,7 +649,7 @@ int check_flags(nnp_handle* h, hipStream_t stream, Common& cm, nnp_status* st, b
   const int was = ahead ? h->lcap : 0;
   set_lcap(h, cm.layout);
   if (!ahead) return 0;
-  if (h->lcap > was) return 2;
+  if (h->lcap > was) return 1;
   h->lcap = was;  // what this call's rows and masks are laid out for
   return 0;
 }
@@ -663,10 +678,10 @@ constexpr size_t PAIR_MASK_MAX_BYTES = (size_t)16 << 30;
 constexpr int PAIR_MASK_MIN_NEIGHBORS = 64;
 
 // Calls of at most this many atoms launch every pass behind the neighbour build
-// at once, with the row capacity that the handle's last call needed (lcap_next),
-// and look at the build's flags afterwards; where they say that the passes could
-// not run (Gate), the call goes on as a first call does: wait for the flags, then
-// launch.  That wait in the middle left the GPU idle for 12 us: water of 192 atoms
+// at once, on rows cut at the capacity that the handle's last calls needed
+// (lcap_next), and look at the build's flags afterwards; where a row was cut or the
+// inputs were refused, nothing is written to the caller (Gate), and the call goes
+// on as a first call does: build, wait for the flags, launch.  That wait in the middle left the GPU idle for 12 us: water of 192 atoms
 // 97 -> 84 us, 1,029 in FP64 176 -> 163 us, 12,288 281 -> 275 us; three-element
 // 15,147 atoms 422 -> 415 us; 98,304 in BF16 1,513 -> 1,507 us.  Larger calls gain
 // less than 0.5 %, and a capacity of other inputs could cost them occupancy.
@@ -913,10 +928,8 @@ nnp_status evaluate(nnp_handle* h, Common& cm, Marks& mk, const FwdBufs<P>& b, i
   const int64_t n = cm.B.n;
   const Gate gate = {ahead ? cm.bin.flags : nullptr, h->cap, h->lcap};
   TripArgs<P> ta = trip_args<P>(h, cm);
-  ta.gate = gate;
   MlpArgs<P> ma;
   std::memset(&ma, 0, sizeof(ma));
-  ma.gate = gate;
   if (ahead) {
     ma.host_flags = h->h_flags_dev;
     ma.flags = cm.bin.flags;
@@ -1003,15 +1016,18 @@ nnp_status forward(nnp_handle* h, int n_struct, const int64_t* offs, const void*
   int layout = list_layout<P>(h);
   for (int attempt = 0; attempt < 8; ++attempt) {
     const bool ahead = attempt == 0 && may_run_ahead<P>(h, 0, 1, n, layout);
-    if (ahead) cm.bin.host_flags = nullptr;  // the network pass reports
+    if (ahead) {
+      h->lcap = cm.bin.clip = std::min(h->lcap_next, h->cap);
+      cm.bin.host_flags = nullptr;  // the network pass reports
+    }
     st = build_neighbors<T>(h, cm, stream, attempt == 0, layout);
     cm.bin.host_flags = h->h_flags_dev;
+    cm.bin.clip = INT_MAX;
     if (st) return st;
     if (ahead) {
-      h->lcap = std::min(h->lcap_next, h->cap);
       mk.mark("neighbors");
       if ((st = evaluate<P>(h, cm, mk, bufs, n_struct, pos, types, energies_dev, energy_host, ei_v, f_v, stream, remember,
-                            true, cm.B.total_cells)))
+                            true, count_blocks(cm.B))))
         return st;
     }
     const bool synced = energy_host || h->prof;
@@ -1019,7 +1035,7 @@ nnp_status forward(nnp_handle* h, int n_struct, const int64_t* offs, const void*
     if (r < 0) return st;
     if (ahead && r == 0) return evaluated(h, mk, energy_host, remember, synced, stream);
     if (ahead) mk.restart();
-    if (r == 1) continue;  // capacity grew: rebuild the neighbour list
+    if (r == 1) continue;  // a capacity grew: rebuild the neighbour list
     if (layout != NNP_LIST_PADDED) {
       bool flat = false;
       if ((st = use_flat<P>(h, 0, 1, &flat))) return st;
@@ -1073,7 +1089,7 @@ nnp_status forward_skin(nnp_handle* h, int64_t n, const void* pos_v, const int32
     if (!h->skin_ok) {
       if ((st = prepare<IO>(h, cm, pos, types, stream))) return st;  // clears the flags
       int* cmax = nullptr;
-      if ((st = ensure_t(h, "cmax", std::max(cm.B.total_cells, 1), &cmax))) return st;
+      if ((st = ensure_t(h, "cmax", count_blocks(cm.B), &cmax))) return st;
       launch_neighbor_index(cm.bin, rs, h->scap, snbr, snnb, cmax, stream);
       NNP_HIP(h, hipMemcpyAsync(h->h_flags, cm.bin.flags, 4 * sizeof(int), hipMemcpyDeviceToHost, stream));
       NNP_HIP(h, hipStreamSynchronize(stream));
@@ -1095,12 +1111,13 @@ nnp_status forward_skin(nnp_handle* h, int64_t n, const void* pos_v, const int32
       mk.mark("regather");
     }
     if ((st = bind_neighbors<T>(h, cm))) return st;
+    const bool ahead = attempt == 0 && may_run_ahead<P>(h, 0, 1, n, NNP_LIST_PADDED);
+    if (ahead) h->lcap = cm.bin.clip = std::min(h->lcap_next, h->cap);
+    const int lcap = h->lcap;
     launch_refresh<T>(cm.bin, snbr, snnb, h->scap, h->rc, h->cap, reinterpret_cast<typename Vec4<T>::type*>(cm.nbr),
                       cm.nnb, stream);
-    const bool ahead = attempt == 0 && may_run_ahead<P>(h, 0, 1, n, NNP_LIST_PADDED);
-    int lcap = 0;
+    cm.bin.clip = INT_MAX;
     if (ahead) {
-      h->lcap = lcap = std::min(h->lcap_next, h->cap);
       mk.mark("neighbors");
       if ((st = evaluate<P>(h, cm, mk, bufs, 1, pos, types, energies_dev, nullptr, nullptr, f_v, stream, false, true)))
         return st;
@@ -1126,7 +1143,10 @@ nnp_status forward_skin(nnp_handle* h, int64_t n, const void* pos_v, const int32
       h->lcap = lcap;
       return evaluated(h, mk, nullptr, false, false, stream);
     }
-    if (ahead) mk.restart();
+    if (ahead) {  // a row was cut: refresh again
+      mk.restart();
+      continue;
+    }
     mk.mark("neighbors");
     return evaluate<P>(h, cm, mk, bufs, 1, pos, types, energies_dev, nullptr, nullptr, f_v, stream, false);
   }
@@ -1194,7 +1214,7 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
         ta.pm = h->fwd_pm;
         ta.pm_stride = h->fwd_pm_stride;
       }
-      ta.gate = gate;
+      ta.gate = gate.flags;
       ta.delta = delta;
       ta.V = V;
       if (flat) launch_flat<P>(2, ta, stream);

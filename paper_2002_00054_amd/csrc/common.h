@@ -197,10 +197,10 @@ __device__ inline void wave_sum_many(const Acc (&x)[K], Acc* out, int lane) {
 }
 
 
-// Lets the passes after a neighbour build be launched before the host has seen
-// the build's flags: they do nothing where it failed, or where the rows
-// outgrew what the passes were launched with.  flags: the build's, 16-byte
-// aligned (null: the host has seen them).
+// For kernels launched before the host has seen the flags of the neighbour build
+// (or of the comparison of inputs) they rest on: they write no results where it
+// failed, or where rows outgrew what the passes were launched with.  flags: the
+// build's, 16-byte aligned (null: the host has seen them).
 struct Gate {
   const int* flags;
   int cap, lcap;

@@ -152,7 +152,6 @@ __global__ void __launch_bounds__(256) k_mlp_mfma(MlpArgs<P> a, int wpe) {
     report_flags(a.flags, a.cmax, a.ncells, a.host_flags);
     return;
   }
-  if (gate_closed(a.gate)) return;
   const T* __restrict__ src = a.nets + (size_t)e * NET_STRIDE;
   for (int i = threadIdx.x; i < NET_STRIDE; i += 256) W[i] = src[i];
   if (threadIdx.x < HID) isc[threadIdx.x] = threadIdx.x < MAX_SF ? (T)a.tab->inv_scale_d[e][threadIdx.x] : T(0);

@@ -341,7 +341,8 @@ __global__ void __launch_bounds__(1024) k_sort_small(DescBlob d, int* __restrict
   }
 }
 
-// Neighbour build, one workgroup per cell.  The candidates of the cell (all
+// Neighbour build, one or more workgroups per cell (each takes an equal share of
+// the cell's centres, neighbor_split).  The candidates of the cell (all
 // atoms of the deduplicated 3x3x3 block of cells around it, element by
 // element) are staged in LDS in tiles; each wave then takes centres of the
 // cell in turn, tests 64 candidates per step in FP64 under the minimum image
@@ -352,7 +353,7 @@ __global__ void __launch_bounds__(1024) k_sort_small(DescBlob d, int* __restrict
 // displacement is a plain difference; otherwise the minimum image is taken
 // per pair.  At most cap entries are written per row; the largest count
 // beyond cap goes to flags[1] (the caller grows cap and rebuilds) and the
-// largest count of the cell to cmax[cell].
+// workgroup's largest count to cmax[workgroup].
 // Staged candidates per tile: the most that keeps six workgroups on a CU (26.6
 // KB of LDS each).  A 2M-atom water box stages about 605 candidates per cell,
 // so most cells take one tile: 1.58 -> 1.46 ms against 512-candidate tiles,
@@ -380,10 +381,10 @@ __device__ inline int centre_of(int ci, const int* cbeg, const int* clen, int n_
   return -1;
 }
 
-template <class E>
+template <class E, bool SMALL>
 __global__ void __launch_bounds__(256) k_neighbors(const double4* __restrict__ pos4, const DevStruct* __restrict__ st,
                                                    int n_struct, const int* __restrict__ start, int n_el,
-                                                   int total_cells, double rc2, int cap, E* __restrict__ nbr,
+                                                   int total_cells, double rc2, int cap, int clip, E* __restrict__ nbr,
                                                    int4* __restrict__ nnb, int* __restrict__ flags,
                                                    int* __restrict__ cmax, const int* __restrict__ roff,
                                                    int* __restrict__ host_flags) {
@@ -398,16 +399,16 @@ __global__ void __launch_bounds__(256) k_neighbors(const double4* __restrict__ p
   __shared__ int red[4];
   const int X = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  // Small batches (host_flags set): each workgroup adds its largest count to
-  // flags[2] itself and the last one to finish hands the flags to the host.
+  // The smallest batches (host_flags set): each workgroup adds its largest count
+  // to flags[2] itself and the last one to finish hands the flags to the host.
   auto finish = [&](int m) {
     if (tid != 0) return;
-    if (!host_flags) {
-      cmax[X] = m;
+    if (!SMALL || !host_flags) {
+      cmax[SMALL ? X * gridDim.y + blockIdx.y : X] = m;
       return;
     }
     if (m > 0) atomicMax(&flags[2], m);
-    flags_to_host(flags, host_flags, total_cells);
+    flags_to_host(flags, host_flags, total_cells * gridDim.y);
   };
   int lo = 0, hi = n_struct - 1;
   while (lo < hi) {
@@ -433,7 +434,13 @@ __global__ void __launch_bounds__(256) k_neighbors(const double4* __restrict__ p
       nc += clen[f];
     }
   }
-  if (nc == 0) {
+  int first = 0;  // this workgroup's centres of the cell: [first, nc)
+  if (SMALL) {
+    const int share = (int)((nc + gridDim.y - 1) / gridDim.y);
+    first = min(nc, share * (int)blockIdx.y);
+    nc = min(nc, first + share);
+  }
+  if (first == nc) {
     finish(0);
     return;
   }
@@ -471,7 +478,7 @@ __global__ void __launch_bounds__(256) k_neighbors(const double4* __restrict__ p
   const double L0 = S.L[0], L1 = S.L[1], L2 = S.L[2];
   const double i0 = S.invL[0], i1 = S.invL[1], i2 = S.invL[2];
   int most = 0;
-  for (int cb = 0; cb < nc; cb += NB_MAXC) {
+  for (int cb = first; cb < nc; cb += NB_MAXC) {
     const int nbc = min(NB_MAXC, nc - cb);
     for (int i = tid; i < nbc; i += 256) {
       const int c = centre_of(cb + i, cbeg, clen, n_el);
@@ -529,7 +536,7 @@ __global__ void __launch_bounds__(256) k_neighbors(const double4* __restrict__ p
                                          __builtin_amdgcn_ballot_w64(sidx != c) &
                                          __builtin_amdgcn_ballot_w64(dx * dx + dy * dy + dz * dz < rc2);
           const int rank = tot + lanes_below(msk);
-          const unsigned long long keep = row ? msk & __builtin_amdgcn_ballot_w64(rank < cap) : 0ull;
+          const unsigned long long keep = row ? msk & __builtin_amdgcn_ballot_w64(rank < clip) : 0ull;
           if (__builtin_amdgcn_inverse_ballot_w64(keep))
             *reinterpret_cast<E*>(reinterpret_cast<char*>(row) + (unsigned)rank * (unsigned)sizeof(E)) =
                 make_entry_as<E>(dx, dy, dz, sidx);
@@ -554,10 +561,10 @@ __global__ void __launch_bounds__(256) k_neighbors(const double4* __restrict__ p
     for (int i = tid; i < nbc; i += 256) {
       const int c = cidx[i];
       const int tot = c_tot[i];
-      // rows hold the passing candidates in candidate order, clipped at cap
+      // rows hold the passing candidates in candidate order, cut at clip <= cap
       int kept[MAX_EL + 1];
-      for (int f = 0; f < MAX_EL; ++f) kept[f] = min(f < n_el && c_bnd[i][f] >= 0 ? c_bnd[i][f] : tot, cap);
-      kept[MAX_EL] = min(tot, cap);
+      for (int f = 0; f < MAX_EL; ++f) kept[f] = min(f < n_el && c_bnd[i][f] >= 0 ? c_bnd[i][f] : tot, clip);
+      kept[MAX_EL] = min(tot, clip);
       nnb[c] = make_int4(kept[1] - kept[0], kept[2] - kept[1], kept[3] - kept[2], kept[4] - kept[3]);
       if (tot > cap) atomicMax(&flags[1], tot);
       most = max(most, tot);
@@ -566,7 +573,7 @@ __global__ void __launch_bounds__(256) k_neighbors(const double4* __restrict__ p
   }
   for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
   if (lane == 0) red[wv] = most;
-  if (host_flags) __threadfence();  // this thread's flags[1] atomics before the block is counted as done
+  if (SMALL && host_flags) __threadfence();  // this thread's flags[1] atomics before the block is counted as done
   __syncthreads();
   finish(max(max(red[0], red[1]), max(red[2], red[3])));
 }
@@ -640,7 +647,7 @@ __global__ void __launch_bounds__(256) k_regather(int64_t n, const TIn* __restri
 template <class E>
 __global__ void __launch_bounds__(256) k_refresh(int64_t n, int n_el, const double4* __restrict__ pos4,
                                                  const DevStruct* __restrict__ st, const int* __restrict__ snbr,
-                                                 const int4* __restrict__ snnb, int scap, double rc2, int cap,
+                                                 const int4* __restrict__ snnb, int scap, double rc2, int cap, int clip,
                                                  E* __restrict__ nbr, int4* __restrict__ nnb,
                                                  int* __restrict__ flags) {
   __shared__ int red[4];
@@ -675,10 +682,10 @@ __global__ void __launch_bounds__(256) k_refresh(int64_t n, int n_el, const doub
         }
         const unsigned long long msk = __builtin_amdgcn_ballot_w64(pass);
         const int rank = tot + lanes_below(msk);
-        if (pass && rank < cap) row[rank] = make_entry_as<E>(dx, dy, dz, j);
+        if (pass && rank < clip) row[rank] = make_entry_as<E>(dx, dy, dz, j);
         tot += __popcll(msk);
       }
-      kept[f] = min(tot, cap) - min(before, cap);
+      kept[f] = min(tot, clip) - min(before, clip);
       so = end;
     }
     if (lane == 0) nnb[c] = make_int4(kept[0], kept[1], kept[2], kept[3]);
@@ -803,17 +810,37 @@ template void launch_bin_sort<double>(const BinArgs&, const double*, hipStream_t
 // larger batches keep per-cell counts and the grid of k_max_count, whose blocks
 // take 4,096 cells each.
 constexpr int DIRECT_MAX_CELLS = 32;
+
+// A cell's centres are shared among several workgroups, as long as all of them
+// fit on the 256 CUs at once (six each) and a wave keeps a centre: one workgroup
+// per cell leaves most of the CUs without work in small boxes, and the rest wait
+// on their own loads.  Build kernel at one workgroup per cell and shared: water of
+// 1,029 atoms (FP64, 27 cells) 51 -> 16 us, 12,288 (512 cells) 33 -> 27 us, 15,147
+// atoms of three elements (715 cells) 49 -> 40 us; with more than fit at once
+// 12,288 takes 31 us.  From 1,536 / 2 cells on (around 18,000 water atoms) there
+// is one each.
+constexpr int NB_BLOCKS = 1536;
+int neighbor_split(int64_t n, int total_cells) {
+  if (total_cells >= NB_BLOCKS) return 1;
+  const int64_t per_wave = (n + 4 * (int64_t)total_cells - 1) / (4 * (int64_t)total_cells);  // centres
+  return (int)std::max<int64_t>(1, std::min<int64_t>({NB_BLOCKS / std::max(total_cells, 1), per_wave}));
+}
 template <class E>
 void launch_neighbors_as(const BinArgs& a, double rc, int cap, E* nbr, int4* nnb, int* cmax, hipStream_t stream,
                          const int* roff = nullptr) {
   if (a.n == 0) return;
-  const bool small = a.host_flags && a.total_cells <= DIRECT_MAX_CELLS;
-  hipLaunchKernelGGL(k_neighbors<E>, dim3((unsigned)a.total_cells), dim3(256), 0, stream, a.pos4, a.st, a.n_struct,
-                     a.start, a.n_el, a.total_cells, rc * rc, cap, nbr, nnb, a.flags, cmax, roff,
-                     small ? a.host_flags : nullptr);
+  const int split = neighbor_split(a.n, a.total_cells), blocks = a.total_cells * split;
+  const bool small = a.host_flags && blocks <= DIRECT_MAX_CELLS;
+  if (small || split > 1)
+    hipLaunchKernelGGL((k_neighbors<E, true>), dim3((unsigned)a.total_cells, (unsigned)split), dim3(256), 0, stream, a.pos4,
+                       a.st, a.n_struct, a.start, a.n_el, a.total_cells, rc * rc, cap, std::min(cap, a.clip), nbr, nnb, a.flags, cmax, roff,
+                       small ? a.host_flags : nullptr);
+  else
+    hipLaunchKernelGGL((k_neighbors<E, false>), dim3((unsigned)a.total_cells), dim3(256), 0, stream, a.pos4, a.st,
+                       a.n_struct, a.start, a.n_el, a.total_cells, rc * rc, cap, std::min(cap, a.clip), nbr, nnb, a.flags, cmax, roff, nullptr);
   if (small || !a.host_flags) return;
-  hipLaunchKernelGGL(k_max_count, dim3((unsigned)std::max(1, (a.total_cells + MAXC_PER - 1) / MAXC_PER)), dim3(256), 0,
-                     stream, a.total_cells, cmax, a.flags, a.host_flags);
+  hipLaunchKernelGGL(k_max_count, dim3((unsigned)std::max(1, (blocks + MAXC_PER - 1) / MAXC_PER)), dim3(256), 0, stream,
+                     blocks, cmax, a.flags, a.host_flags);
 }
 
 template <class T>
@@ -876,7 +903,7 @@ void launch_refresh(const BinArgs& a, const int* snbr, const int4* snnb, int sca
   if (a.n == 0) return;
   const unsigned g = (unsigned)std::min<int64_t>((a.n + 3) / 4, 16384);
   hipLaunchKernelGGL(k_refresh<typename Vec4<T>::type>, dim3(g), dim3(256), 0, stream, a.n, a.n_el, a.pos4, a.st,
-                     snbr, snnb, scap, rc * rc, cap, nbr, nnb, a.flags);
+                     snbr, snnb, scap, rc * rc, cap, std::min(cap, a.clip), nbr, nnb, a.flags);
 }
 template void launch_refresh<float>(const BinArgs&, const int*, const int4*, int, double, int, float4*, int4*,
                                     hipStream_t);

@@ -28,6 +28,7 @@ struct BinArgs {
                              // [4] workgroups of the neighbour build that are done
   int* host_flags;           // pinned copy of [0..3], written at the end of the neighbour build;
                              // null: the build leaves its counts in cmax for the network pass
+  int clip;                  // rows are cut at this many entries (counted in full)
   int* desc;                 // device block of the batch description (st, soff, ...)
   const void* desc_host;     // its contents, if the sort is to write them (at most DESC_BLOB_BYTES), else null
   size_t desc_bytes;
@@ -39,7 +40,9 @@ void launch_fill_int(int* p, int64_t n, int v, hipStream_t stream);
 // Clears the flags, writes the batch description if it is given, and sorts.
 template <class TIn>
 void launch_bin_sort(const BinArgs& a, const TIn* pos, hipStream_t stream);
-// Neighbour rows of (dx, dy, dz, j) entries; cmax: [total_cells] scratch.
+// Neighbour rows of (dx, dy, dz, j) entries; cmax: [neighbor_split workgroups per
+// cell * total_cells] scratch.
+int neighbor_split(int64_t n, int total_cells);
 template <class T>
 void launch_neighbors(const BinArgs& a, double rc, int cap, typename Vec4<T>::type* nbr, int4* nnb, int* cmax,
                       hipStream_t stream);
@@ -87,6 +90,7 @@ struct TripArgs {
   const int* roff;           // null: row c at c * cap; else compact rows at roff[c] (wave-level passes only)
   int wpc;                   // waves per centre of the wave-level passes (1 or 2)
   const int4* nnb;           // [n] neighbours per element block
+  const int* gate;           // JVP: Gate::flags, with cap and lcap
   const DevStruct* st;
   const DevTab<T>* tab;
   IO* G;                     // SF: G~ rows [n][LD]
@@ -102,7 +106,6 @@ struct TripArgs {
   unsigned* pm;
   int pm_stride;
   int poly;                  // FP64: the table's X_n polynomials are accurate (DevTab::xpoly)
-  Gate gate;
 };
 
 // Most steps the one-wave pair walk can take for a centre with m neighbours
@@ -193,7 +196,6 @@ struct MlpArgs {
   IO* Ei;                    // [n] atomic energies (sorted)
   const T* nets;             // [n_el][NET_STRIDE] padded parameters
   typename Types<P>::FAcc* F;  // force accumulator [3][n], cleared here for the force pass
-  Gate gate;
   // With host_flags, one more workgroup sets flags[2] to the largest of
   // cmax[0 .. ncells) (and of itself) and copies flags[0..3] to the host.
   int* host_flags;
