@@ -1170,8 +1170,7 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
   Marks mk(h, stream);
   (void)hipGetLastError();
   IO *G, *V, *delta;
-  double *gE_atom, *part, *padded;
-  T* vec;
+  double* part;
   const int64_t n1 = std::max<int64_t>(n, 1);
   // atoms per chunk of the weight-gradient reduction: 64, or more once there
   // would be over 4096 chunks (bounds the FP64 partial sums)
@@ -1180,10 +1179,7 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
   if ((st = ensure_t(h, "G", (size_t)n1 * LD, &G))) return st;
   if ((st = ensure_t(h, "V", (size_t)n1 * LD, &V))) return st;
   if ((st = ensure_t(h, "delta", (size_t)n1 * 3, &delta))) return st;
-  if ((st = ensure_t(h, "gE_atom", n1, &gE_atom))) return st;
-  if ((st = ensure_t(h, "wvec", (size_t)n1 * 11 * HID, &vec))) return st;
   if ((st = ensure_t(h, "wpart", (size_t)h->n_el * nch * NET_STRIDE, &part))) return st;
-  if ((st = ensure_t(h, "wpad", (size_t)h->n_el * NET_STRIDE, &padded))) return st;
   // With the inputs of the last batch forward, its sorted order, neighbour
   // list and G~ (and J store) are reused: only the force-adjoint product and
   // the weight gradient run.  Otherwise they are rebuilt first.
@@ -1221,7 +1217,6 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
       else launch_wave<P>(h, 2, ta, stream);
     }
     mk.mark("jvp");
-    launch_gather_struct_grad(n, cm.bin.perm, cm.d_soff, n_struct, dL_dE, gE_atom, stream);
     WGradArgs<P> wa;
     std::memset(&wa, 0, sizeof(wa));
     wa.n = n;
@@ -1229,14 +1224,13 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
     wa.eoff = cm.bin.eoff;
     wa.G = G;
     wa.V = V;
-    wa.gE_atom = gE_atom;
+    wa.gE = dL_dE;
+    wa.pos4 = cm.bin.pos4;
     wa.nets = reinterpret_cast<const T*>(h->d_nets);
     wa.tab = reinterpret_cast<const DevTab<T>*>(h->d_tab);
-    wa.vec = vec;
     wa.chunk = chunk;
     wa.nch = nch;
     wa.partial = part;
-    wa.padded = padded;
     wa.n_params = (int64_t)h->params.size();
     wa.flatmap = h->d_flatmap;
     wa.out = grad;

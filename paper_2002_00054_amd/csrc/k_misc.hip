@@ -72,32 +72,6 @@ void launch_permute_rows3(int64_t n, const int* perm, const IO* in, IO* out, hip
 template void launch_permute_rows3<float>(int64_t, const int*, const float*, float*, hipStream_t);
 template void launch_permute_rows3<double>(int64_t, const int*, const double*, double*, hipStream_t);
 
-// gE_atom[s] = gE[structure of caller atom perm[s]] (0 if gE is null).
-__global__ void __launch_bounds__(256) k_gather_struct_grad(int64_t n, const int* __restrict__ perm,
-                                                            const int64_t* __restrict__ soff, int n_struct,
-                                                            const double* __restrict__ gE, double* __restrict__ out) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  if (!gE) {
-    out[s] = 0.0;
-    return;
-  }
-  const int64_t i = perm[s];
-  int lo = 0, hi = n_struct - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (soff[mid] <= i) lo = mid; else hi = mid - 1;
-  }
-  out[s] = gE[lo];
-}
-
-void launch_gather_struct_grad(int64_t n, const int* perm, const int64_t* soff, int n_struct, const double* gE,
-                               double* gE_atom, hipStream_t stream) {
-  if (n <= 0) return;
-  hipLaunchKernelGGL(k_gather_struct_grad, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, n, perm, soff,
-                     n_struct, gE, gE_atom);
-}
-
 // Block tree sum of a range in a fixed order.
 __device__ inline double block_sum_256(double v) {
   __shared__ double sh[256];

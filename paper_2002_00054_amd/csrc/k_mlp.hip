@@ -220,207 +220,195 @@ void launch_mlp(const MlpArgs<P>& a, hipStream_t stream) {
 }
 
 // ------------------------------------------------------------ weight gradient
-// Per-atom vectors of the forward-over-reverse pass, stored for the
-// parameter reduction:  [x, t, h1, dh1, zb1, dzb1, h2, dh2, zb2, dzb2, alpha]
-// where t is the tangent (JVP row / scale), dh = tangent of h, zb/dzb the
-// adjoints of the pre-activations of the primal and tangent chains.
-constexpr int WG_VEC = 11;
-
-// One atom per 32 lanes (two per wave): lane l owns hidden unit l, so every
-// layer is one 32-term dot product per lane (a row of W, read four at a time)
-// whose inputs come from the atom's other lanes by width-32 shuffles; the
-// backward step through W2 has lane l own input l (a column of W2, read
-// coalesced across the lanes).  Same expressions and summation order as one
-// thread per atom, with 32 times the parallelism.
-template <int P>
-__global__ void __launch_bounds__(256) k_wgrad_atoms(WGradArgs<P> a) {
-  using T = typename Types<P>::T;
-  using V4 = typename Vec4<T>::type;
-  constexpr int ATOMS = 256 / HID;  // atoms per block
-  if (gate_closed(a.gate)) return;
-  int e;
-  int64_t r0, r1;
-  if (!element_tile(blockIdx.x, ATOMS, a.n_el, a.eoff, e, r0, r1)) return;
-  e = uniform(e);
-  const int l = threadIdx.x & (HID - 1);
-  const int64_t r = r0 + (threadIdx.x / HID);
-  if (r >= r1) return;  // the atom's 32 lanes leave together
-  const T* __restrict__ W = a.nets + (size_t)e * NET_STRIDE;
-  T* out = a.vec + r * (WG_VEC * HID);
-  const T x = (T)a.G[r * LD + l];
-  const T t = (T)a.V[r * LD + l] * (l < MAX_SF ? (T)a.tab->inv_scale_d[e][l] : T(0));
-  // layer 1: z = W1 x + b1 and its tangent W1 t (lane = output unit)
-  T z = W[OFF_B1 + l], dz = T(0);
-#pragma unroll
-  for (int kb = 0; kb < HID; kb += 4) {
-    const V4 w = *reinterpret_cast<const V4*>(W + OFF_W1 + l * HID + kb);
-    const T wk[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      z += wk[q] * __shfl(x, kb + q, HID);
-      dz += wk[q] * __shfl(t, kb + q, HID);
-    }
-  }
-  const T h1 = tanh_t(z), dz1 = dz;
-  const T dh1 = (T(1) - h1 * h1) * dz1;
-  out[0 * HID + l] = x;
-  out[1 * HID + l] = t;
-  out[2 * HID + l] = h1;
-  out[3 * HID + l] = dh1;
-  const T alpha = a.gE_atom ? (T)a.gE_atom[r] : T(0);
-  // layer 2.  Objective J = alpha E - w3 . dh2, dh2 = (1 - h2^2) dz2.
-  T z2 = W[OFF_B2 + l], dz2 = T(0);
-#pragma unroll
-  for (int kb = 0; kb < HID; kb += 4) {
-    const V4 w = *reinterpret_cast<const V4*>(W + OFF_W2 + l * HID + kb);
-    const T wk[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      z2 += wk[q] * __shfl(h1, kb + q, HID);
-      dz2 += wk[q] * __shfl(dh1, kb + q, HID);
-    }
-  }
-  const T h2 = tanh_t(z2);
-  const T g2 = T(1) - h2 * h2;
-  const T w3 = W[OFF_W3 + l];
-  // adjoint of h2: alpha w3 from E, and from -w3 . (1 - h2^2) dz2: +2 w3 h2 dz2
-  const T h2bar = alpha * w3 + T(2) * w3 * h2 * dz2;
-  const T zb2 = g2 * h2bar, dzb2 = -g2 * w3;
-  out[6 * HID + l] = h2;
-  out[7 * HID + l] = g2 * dz2;
-  out[8 * HID + l] = zb2;
-  out[9 * HID + l] = dzb2;
-  // back through W2 (lane = input unit of layer 2)
-  T hb = T(0), dhb = T(0);
-#pragma unroll
-  for (int o = 0; o < HID; ++o) {
-    const T w = W[OFF_W2 + o * HID + l];
-    hb += w * __shfl(zb2, o, HID);
-    dhb += w * __shfl(dzb2, o, HID);
-  }
-  const T g1 = T(1) - h1 * h1;
-  // dh1 = (1 - h1^2) dz1 contributes -2 h1 dz1 dhb to the adjoint of h1
-  hb += dhb * (T(-2) * h1 * dz1);
-  out[4 * HID + l] = g1 * hb;
-  out[5 * HID + l] = g1 * dhb;
-  if (l == 0) out[10 * HID] = alpha;
-}
-
+// One workgroup per chunk of atoms of one element: eight atoms at a time go
+// through the forward-over-reverse pass (a.chunk / 8 rounds), and their outer
+// products are added to the chunk's partial gradient, all parameters in FP64.
+//
+// Pass: one atom per 32 lanes, lane l owning hidden unit l with its rows of W1
+// and W2 in registers for the whole chunk (and its column of W2 in LDS), so that
+// every layer is one 32-term product per lane whose inputs come from the atom's
+// other lanes through LDS (broadcast reads of two (value, tangent) pairs each).  With t
+// the tangent (JVP row / scale): dh the tangent of h, zb / dzb the adjoints of
+// the pre-activations of the primal and the tangent chain.
+//
+// Sums (W1: zb1 x^T + dzb1 t^T, W2: zb2 h1^T + dzb2 dh1^T): thread t owns the 2 x
+// 2 tile at (o, k) = (2 (t / 16), 2 (t % 16)) of both matrices, threads 0-31 also
+// b1, b2 and w3 at index t, thread 32 b3, and threads 33-63 the padding (zero).
+//
+// The eleven vectors of an atom stay in LDS: written to memory by a kernel of
+// their own and read back by one per (chunk, element), with the rows of W read by
+// every atom and one chunk's atoms loaded one after another, the two took 42 + 60
+// us for 30,108 atoms (FP32); this one takes 38 us (FP64 110 -> 64).
 template <class T> struct PairOf;
 template <> struct PairOf<float> { using type = float2; };
 template <> struct PairOf<double> { using type = double2; };
 
-// partial[(e * nch + ch) * NET_STRIDE + p]: sum over one chunk of atoms of
-// element e of the per-atom gradient of every parameter p (padded layout), in
-// FP64.  One 256-thread block per (chunk, element) covers all parameters, so
-// each atom's vector is read once per chunk.  The weight gradients are outer
-// products (W1: zb1 x^T + dzb1 t^T, W2: zb2 h1^T + dzb2 dh1^T): thread t owns
-// the 2 x 2 tile at (o, k) = (2 (t / 16), 2 (t % 16)) of both matrices and
-// reads four pairs of each per atom.  Threads 0-31 also own b1, b2 and w3 at
-// index t, thread 32 owns b3, and threads 33-63 write the padding (zero).
+// w . v and w . dv over an atom's 32 (v, dv) pairs, added to z and dz in order
 template <class T>
-__global__ void __launch_bounds__(256) k_wgrad_chunks(const int* __restrict__ eoff, int chunk, int nch,
-                                                      const T* __restrict__ vec, double* __restrict__ partial,
-                                                      Gate gate) {
-  if (gate_closed(gate)) return;
-  using T2 = typename PairOf<T>::type;
-  static_assert(HID == 32 && NET_STRIDE == OFF_B3 + HID, "tile map covers the padded layout exactly");
-  const int e = blockIdx.y;
-  const int ch = blockIdx.x;
-  const int t = threadIdx.x;
-  const int o0 = 2 * (t >> 4), k0 = 2 * (t & 15);
-  const int64_t lo = eoff[e] + (int64_t)ch * chunk;
-  const int64_t hi = min((int64_t)eoff[e + 1], lo + chunk);
-  double w1[2][2] = {{0.0, 0.0}, {0.0, 0.0}}, w2[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-  double b1 = 0.0, b2 = 0.0, w3 = 0.0, b3 = 0.0;
-  for (int64_t r = lo; r < hi; ++r) {
-    const T* v = vec + r * (WG_VEC * HID);
-    const T2 zb1 = *reinterpret_cast<const T2*>(v + 4 * HID + o0);
-    const T2 dzb1 = *reinterpret_cast<const T2*>(v + 5 * HID + o0);
-    const T2 x = *reinterpret_cast<const T2*>(v + 0 * HID + k0);
-    const T2 tg = *reinterpret_cast<const T2*>(v + 1 * HID + k0);
-    const T2 zb2 = *reinterpret_cast<const T2*>(v + 8 * HID + o0);
-    const T2 dzb2 = *reinterpret_cast<const T2*>(v + 9 * HID + o0);
-    const T2 h1 = *reinterpret_cast<const T2*>(v + 2 * HID + k0);
-    const T2 dh1 = *reinterpret_cast<const T2*>(v + 3 * HID + k0);
-    const T a_o[2] = {zb1.x, zb1.y}, c_o[2] = {dzb1.x, dzb1.y}, b_k[2] = {x.x, x.y}, d_k[2] = {tg.x, tg.y};
-    const T p_o[2] = {zb2.x, zb2.y}, q_o[2] = {dzb2.x, dzb2.y}, u_k[2] = {h1.x, h1.y}, w_k[2] = {dh1.x, dh1.y};
+__device__ inline void dot_pairs(const T (&w)[HID], const typename Vec4<T>::type* pairs, T& z, T& dz) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        w1[i][j] += (double)(a_o[i] * b_k[j] + c_o[i] * d_k[j]);
-        w2[i][j] += (double)(p_o[i] * u_k[j] + q_o[i] * w_k[j]);
-      }
-    if (t < HID) {
-      b1 += (double)v[4 * HID + t];
-      b2 += (double)v[8 * HID + t];
-      w3 += (double)(v[10 * HID] * v[6 * HID + t] - v[7 * HID + t]);
-    } else if (t == HID) {
-      b3 += (double)v[10 * HID];
-    }
+  for (int k = 0; k < HID; k += 2) {
+    const typename Vec4<T>::type p = pairs[k / 2];
+    z += w[k] * p.x;
+    dz += w[k] * p.y;
+    z += w[k + 1] * p.z;
+    dz += w[k + 1] * p.w;
   }
-  double* out = partial + ((size_t)e * nch + ch) * NET_STRIDE;
+}
+
+template <int P>
+__global__ void __launch_bounds__(256, 2) k_wgrad(WGradArgs<P> a) {
+  using T = typename Types<P>::T;
+  using T2 = typename PairOf<T>::type;
+  using V4 = typename Vec4<T>::type;
+  constexpr int ATOMS = 256 / HID;  // atoms per round
+  static_assert(HID == 32 && NET_STRIDE == OFF_B3 + HID, "tile map covers the padded layout exactly");
+  __shared__ V4 xt[ATOMS][HID / 2], hh[ATOMS][HID / 2], zz1[ATOMS][HID / 2], zz2[ATOMS][HID / 2];  // pairs
+  __shared__ T w3g[ATOMS][HID], alphas[ATOMS], W2[HID][HID];
+  if (gate_closed(a.gate)) return;
+  int e;
+  int64_t lo, hi;
+  if (!element_tile(blockIdx.x, a.chunk, a.n_el, a.eoff, e, lo, hi)) return;
+  hi = lo + a.chunk < hi ? lo + a.chunk : hi;
+  e = uniform(e);
+  const int t = threadIdx.x, l = t & (HID - 1), g = t / HID;
+  const T* __restrict__ W = a.nets + (size_t)e * NET_STRIDE;
+  T r1[HID], r2[HID];  // row l of W1 and of W2
+#pragma unroll
+  for (int k = 0; k < HID; k += 4) {
+    const V4 u = *reinterpret_cast<const V4*>(W + OFF_W1 + l * HID + k);
+    const V4 v = *reinterpret_cast<const V4*>(W + OFF_W2 + l * HID + k);
+    r1[k] = u.x, r1[k + 1] = u.y, r1[k + 2] = u.z, r1[k + 3] = u.w;
+    r2[k] = v.x, r2[k + 1] = v.y, r2[k + 2] = v.z, r2[k + 3] = v.w;
+  }
+  for (int i = t; i < HID * HID; i += 256) W2[i / HID][i % HID] = W[OFF_W2 + i];
+  __syncthreads();
+  const T b1 = W[OFF_B1 + l], b2 = W[OFF_B2 + l], w3 = W[OFF_W3 + l];
+  const T inv_scale = l < MAX_SF ? (T)a.tab->inv_scale_d[e][l] : T(0);
+  const int to = t >> 4, tk = t & 15;  // the tile's pairs
+  double w1s[2][2] = {{0.0, 0.0}, {0.0, 0.0}}, w2s[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+  double b1s = 0.0, b2s = 0.0, w3s = 0.0, b3s = 0.0;
+  for (int64_t base = lo; base < hi; base += ATOMS) {
+    const int64_t r = base + g;
+    if (r < hi) {
+      T2 pair;
+      pair.x = (T)a.G[r * LD + l];
+      pair.y = (T)a.V[r * LD + l] * inv_scale;
+      reinterpret_cast<T2*>(xt[g])[l] = pair;
+      const T alpha = a.gE ? (T)a.gE[struct_of(a.pos4[r].w)] : T(0);
+      __builtin_amdgcn_wave_barrier();
+      // layer 1: z = W1 x + b1 and its tangent W1 t
+      T z = b1, dz1 = T(0);
+      dot_pairs<T>(r1, xt[g], z, dz1);
+      const T h1 = tanh_t(z);
+      const T dh1 = (T(1) - h1 * h1) * dz1;
+      pair.x = h1;
+      pair.y = dh1;
+      reinterpret_cast<T2*>(hh[g])[l] = pair;
+      __builtin_amdgcn_wave_barrier();
+      // layer 2.  Objective J = alpha E - w3 . dh2, dh2 = (1 - h2^2) dz2.
+      T z2 = b2, dz2 = T(0);
+      dot_pairs<T>(r2, hh[g], z2, dz2);
+      const T h2 = tanh_t(z2);
+      const T g2 = T(1) - h2 * h2;
+      // adjoint of h2: alpha w3 from E, and from -w3 . (1 - h2^2) dz2: +2 w3 h2 dz2
+      const T h2bar = alpha * w3 + T(2) * w3 * h2 * dz2;
+      pair.x = g2 * h2bar;
+      pair.y = -g2 * w3;
+      reinterpret_cast<T2*>(zz2[g])[l] = pair;
+      const T dh2 = g2 * dz2;
+      w3g[g][l] = alpha * h2 - dh2;
+      if (l == 0) alphas[g] = alpha;
+      __builtin_amdgcn_wave_barrier();
+      // back through W2 (lane = input unit of layer 2)
+      T c2[HID], hb = T(0), dhb = T(0);
+#pragma unroll
+      for (int o = 0; o < HID; ++o) c2[o] = W2[o][l];
+      dot_pairs<T>(c2, zz2[g], hb, dhb);
+      const T g1 = T(1) - h1 * h1;
+      // dh1 = (1 - h1^2) dz1 contributes -2 h1 dz1 dhb to the adjoint of h1
+      hb += dhb * (T(-2) * h1 * dz1);
+      pair.x = g1 * hb;
+      pair.y = g1 * dhb;
+      reinterpret_cast<T2*>(zz1[g])[l] = pair;
+    }
+    __syncthreads();
+    const int na = (int)(hi - base < ATOMS ? hi - base : ATOMS);
+    for (int q = 0; q < na; ++q) {
+      const V4 zo = zz1[q][to], xk = xt[q][tk], po = zz2[q][to], hk = hh[q][tk];
+      const T a_o[2] = {zo.x, zo.z}, c_o[2] = {zo.y, zo.w}, b_k[2] = {xk.x, xk.z}, d_k[2] = {xk.y, xk.w};
+      const T p_o[2] = {po.x, po.z}, q_o[2] = {po.y, po.w}, u_k[2] = {hk.x, hk.z}, v_k[2] = {hk.y, hk.w};
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          w1s[i][j] += (double)(a_o[i] * b_k[j] + c_o[i] * d_k[j]);
+          w2s[i][j] += (double)(p_o[i] * u_k[j] + q_o[i] * v_k[j]);
+        }
+      if (t < HID) {
+        b1s += (double)reinterpret_cast<const T2*>(zz1[q])[t].x;
+        b2s += (double)reinterpret_cast<const T2*>(zz2[q])[t].x;
+        w3s += (double)w3g[q][t];
+      } else if (t == HID) {
+        b3s += (double)alphas[q];
+      }
+    }
+    __syncthreads();  // the round's vectors are read
+  }
+  const int ch = (int)((lo - a.eoff[e]) / a.chunk);
+  double* out = a.partial + ((size_t)e * a.nch + ch) * NET_STRIDE;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      out[OFF_W1 + (o0 + i) * HID + k0 + j] = w1[i][j];
-      out[OFF_W2 + (o0 + i) * HID + k0 + j] = w2[i][j];
+      out[OFF_W1 + (2 * to + i) * HID + 2 * tk + j] = w1s[i][j];
+      out[OFF_W2 + (2 * to + i) * HID + 2 * tk + j] = w2s[i][j];
     }
   if (t < HID) {
-    out[OFF_B1 + t] = b1;
-    out[OFF_B2 + t] = b2;
-    out[OFF_W3 + t] = w3;
+    out[OFF_B1 + t] = b1s;
+    out[OFF_B2 + t] = b2s;
+    out[OFF_W3 + t] = w3s;
   } else if (t == HID) {
-    out[OFF_B3] = b3;
-  } else if (t < 2 * HID) {
-    out[OFF_B3 + (t - HID)] = 0.0;
+    out[OFF_B3] = b3s;
   }
 }
 
-// out[e][p] = sum over the chunks of element e (FP64) in a fixed order: eight
-// running sums, chunk ch going to sum ch % 8 in chunk order, then the eight
-// in order.  A block covers 32 parameters with 8 threads each.
-__global__ void __launch_bounds__(256) k_wgrad_final(int nch, const double* __restrict__ partial,
-                                                     double* __restrict__ out) {
+// The gradient in the caller's layout: for each parameter the sum over the
+// chunks of its element in a fixed order: eight running sums, chunk ch going to
+// sum ch % 8 in chunk order, then the eight in order.  A block covers 32
+// parameters with 8 threads each.
+__global__ void __launch_bounds__(256) k_wgrad_final(int64_t np, const int* __restrict__ map,
+                                                     const int* __restrict__ eoff, int chunk, int nch,
+                                                     const double* __restrict__ partial, double* __restrict__ out,
+                                                     Gate gate) {
   __shared__ double red[8][32];
-  const int e = blockIdx.y;
+  if (gate_closed(gate)) return;
   const int pl = threadIdx.x & 31, g = threadIdx.x >> 5;
-  const int p = blockIdx.x * 32 + pl;
+  const int64_t i = (int64_t)blockIdx.x * 32 + pl;
   double s = 0.0;
-  if (p < NET_STRIDE)
-    for (int ch = g; ch < nch; ch += 8) s += partial[((size_t)e * nch + ch) * NET_STRIDE + p];
+  if (i < np) {
+    const int e = map[i] / NET_STRIDE, used = min(nch, (eoff[e + 1] - eoff[e] + chunk - 1) / chunk);
+    const double* p = partial + (size_t)e * nch * NET_STRIDE + (map[i] - e * NET_STRIDE);
+    // eight loads in flight per thread
+#pragma unroll 8
+    for (int ch = g; ch < used; ch += 8) s += p[(size_t)ch * NET_STRIDE];
+  }
   red[g][pl] = s;
   __syncthreads();
-  if (g == 0 && p < NET_STRIDE) {
+  if (g == 0 && i < np) {
     double tot = 0.0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) tot += red[i][pl];
-    out[(size_t)e * NET_STRIDE + p] = tot;
+    for (int k = 0; k < 8; ++k) tot += red[k][pl];
+    out[i] = tot;
   }
-}
-
-// Padded gradient -> caller's flat parameter layout.
-__global__ void __launch_bounds__(256) k_unpad(int64_t np, const int* __restrict__ map, const double* __restrict__ padded,
-                                               double* __restrict__ flat, Gate gate) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < np && !gate_closed(gate)) flat[i] = padded[map[i]];
 }
 
 template <int P>
 void launch_wgrad(const WGradArgs<P>& a, hipStream_t stream) {
-  using T = typename Types<P>::T;
-  if (a.n > 0) {
-    const unsigned g = (unsigned)((a.n + 256 / HID - 1) / (256 / HID) + a.n_el);
-    hipLaunchKernelGGL(k_wgrad_atoms<P>, dim3(g), dim3(256), 0, stream, a);
-  }
-  hipLaunchKernelGGL(k_wgrad_chunks<T>, dim3((unsigned)a.nch, a.n_el), dim3(256), 0, stream, a.eoff, a.chunk, a.nch,
-                     (const T*)a.vec, a.partial, a.gate);
-  hipLaunchKernelGGL(k_wgrad_final, dim3((NET_STRIDE + 31) / 32, a.n_el), dim3(256), 0, stream, a.nch, a.partial,
-                     a.padded);
-  hipLaunchKernelGGL(k_unpad, dim3((unsigned)((a.n_params + 255) / 256)), dim3(256), 0, stream, a.n_params, a.flatmap,
-                     a.padded, a.out, a.gate);
+  if (a.n > 0)  // an element's last chunk may be short: at most one more each
+    hipLaunchKernelGGL(k_wgrad<P>, dim3((unsigned)((a.n + a.chunk - 1) / a.chunk + a.n_el)), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(k_wgrad_final, dim3((unsigned)((a.n_params + 31) / 32)), dim3(256), 0, stream, a.n_params, a.flatmap,
+                     a.eoff, a.chunk, a.nch, a.partial, a.out, a.gate);
 }
 
 template void launch_mlp<P_FP64>(const MlpArgs<P_FP64>&, hipStream_t);

@@ -218,13 +218,12 @@ struct WGradArgs {
   const int* eoff;
   const IO* G;               // [n][LD] scaled inputs
   const IO* V;               // [n][LD] JVP rows (raw G)
-  const double* gE_atom;     // [n] dL/dE of each atom's structure (sorted), or null
+  const double* gE;          // [structures] dL/dE, or null
+  const double4* pos4;       // [n] sorted positions with the structure ids
   const T* nets;
   const DevTab<T>* tab;
-  T* vec;                    // [n][11 * HID] per-atom vectors
   int chunk, nch;            // atoms per partial, partials per element (>= ceil(max N_e / chunk))
   double* partial;           // [n_el][nch][NET_STRIDE]
-  double* padded;            // [n_el][NET_STRIDE]
   int64_t n_params;
   const int* flatmap;        // [n_params] flat index -> padded index
   double* out;               // [n_params] caller layout
@@ -241,8 +240,6 @@ void launch_unpermute(int64_t n, const int* perm, const IO* Ei_s, const FAcc* F_
                       IO* F_out, const Gate& gate, hipStream_t stream);
 template <class IO>
 void launch_permute_rows3(int64_t n, const int* perm, const IO* in, IO* out, hipStream_t stream);
-void launch_gather_struct_grad(int64_t n, const int* perm, const int64_t* soff, int n_struct, const double* gE,
-                               double* gE_atom, hipStream_t stream);
 // Deterministic energy sums: chunk partials then per-structure sums (the chunk
 // sums alone where every structure is one chunk).  host (may be null): pinned,
 // receives the first structure's energy.
