@@ -337,7 +337,8 @@ nnp_status make_batch(nnp_handle* h, int n_struct, const int64_t* offs, const do
   B.n = offs[n_struct];
   if (B.n > (int64_t)INT32_MAX / 2) return fail(h, NNP_E_ARG, "too many atoms");
   int64_t cells = 0;
-  const int64_t chunk = 4096;
+  // atoms per partial sum of a structure's energy: up to here one launch sums it
+  const int64_t chunk = ENERGY_CHUNK;
   for (int b = 0; b < n_struct; ++b) {
     if (offs[b + 1] < offs[b]) return fail(h, NNP_E_ARG, "atom_offsets must be non-decreasing");
     DevStruct s;
@@ -1348,7 +1349,8 @@ nnp_status md_run(nnp_handle* h, int64_t n, void* pos_v, void* vel_v, void* f_v,
   nnp_status st;
   if ((st = ensure_t(h, "md_epot", (size_t)n_steps + 1, &e_dev))) return st;
   if ((st = ensure_t(h, "md_ekin", (size_t)n_steps + 1, &k_dev))) return st;
-  if ((st = ensure_t(h, "md_part", (size_t)md_blocks(n), &part))) return st;
+  const int nb = md_blocks(n);
+  if ((st = ensure_t(h, "md_part", 2 * (size_t)nb, &part))) return st;  // of a step, and of the one before
   const int64_t offs[2] = {0, n};
   h->skin_ok = false;  // the first evaluation builds the skin list
   h->md_builds = 0;
@@ -1358,14 +1360,14 @@ nnp_status md_run(nnp_handle* h, int64_t n, void* pos_v, void* vel_v, void* f_v,
     return forward<P>(h, 1, offs, pos, types, box, e_out, nullptr, nullptr, F, stream);
   };
   if ((st = force_at(e_dev))) return st;
-  int* flags = nullptr;  // cleared by the drift: an evaluation's passes are done with them then
+  int* flags = nullptr;  // cleared with each step: an evaluation's passes are done with them then
   if ((st = ensure_t(h, "flags", N_FLAGS, &flags))) return st;
-  launch_kick_ke<IO>(n, vel, F, types, m, false, part, k_dev, stream);
-  for (int s = 1; s <= n_steps; ++s) {
-    launch_kick_drift<IO>(n, pos, vel, F, types, m, flags, stream);
-    if ((st = force_at(e_dev + s))) return st;
-    launch_kick_ke<IO>(n, vel, F, types, m, true, part, k_dev + s, stream);
+  for (int s = 0; s <= n_steps; ++s) {
+    if (s > 0 && (st = force_at(e_dev + s))) return st;
+    launch_md_step<IO>(n, pos, vel, F, types, m, s > 0, s < n_steps, part + (s & 1) * nb,
+                       s > 0 ? part + (~s & 1) * nb : nullptr, s > 0 ? k_dev + s - 1 : nullptr, flags, stream);
   }
+  launch_ke_total(n, part + (n_steps & 1) * nb, m, k_dev + n_steps, stream);
   if ((st = check_launch(h, "md"))) return st;
   if (epot) NNP_HIP(h, hipMemcpyAsync(epot, e_dev, ((size_t)n_steps + 1) * sizeof(double), hipMemcpyDeviceToHost, stream));
   if (ekin) NNP_HIP(h, hipMemcpyAsync(ekin, k_dev, ((size_t)n_steps + 1) * sizeof(double), hipMemcpyDeviceToHost, stream));

@@ -176,12 +176,12 @@ struct MdArgs {
   double ke_conv;            // amu A^2 / fs^2 -> eV
 };
 int md_blocks(int64_t n);    // blocks of the kinetic-energy partial sums
+// Between two force evaluations (k_md_step).  prev (may be null): the partial sums
+// of the step before, whose kinetic energy goes to ke_prev; flags[0..3] = 0.
 template <class IO>
-void launch_kick_drift(int64_t n, IO* pos, IO* vel, const IO* F, const int32_t* types, const MdArgs& m, int* flags,
-                       hipStream_t stream);  // and flags[0..3] = 0 (flags may be null)
-template <class IO>
-void launch_kick_ke(int64_t n, IO* vel, const IO* F, const int32_t* types, const MdArgs& m, bool kick,
-                    double* partial, double* ke_out, hipStream_t stream);
+void launch_md_step(int64_t n, IO* pos, IO* vel, const IO* F, const int32_t* types, const MdArgs& m, bool kick, bool drift,
+                    double* partial, const double* prev, double* ke_prev, int* flags, hipStream_t stream);
+void launch_ke_total(int64_t n, const double* partial, const MdArgs& m, double* out, hipStream_t stream);
 
 // ---------------------------------------------------------------- K4/K8
 template <int P>
@@ -240,6 +240,7 @@ void launch_unpermute(int64_t n, const int* perm, const IO* Ei_s, const FAcc* F_
                       IO* F_out, const Gate& gate, hipStream_t stream);
 template <class IO>
 void launch_permute_rows3(int64_t n, const int* perm, const IO* in, IO* out, hipStream_t stream);
+constexpr int ENERGY_CHUNK = 16384;
 // Deterministic energy sums: chunk partials then per-structure sums (the chunk
 // sums alone where every structure is one chunk).  host (may be null): pinned,
 // receives the first structure's energy.
