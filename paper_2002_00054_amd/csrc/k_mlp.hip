@@ -137,21 +137,32 @@ __device__ inline void report_flags(int* flags, const int* cmax, int ncells, int
     __hip_atomic_store(&host_flags[i], i == 2 ? m : flags[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Grid: n_el x wpe workgroups of 4 waves (and one that reports the flags); workgroup (e, b) serves element e,
-// its waves striding over that element's 16-atom tiles.  The element's
-// padded weights are staged in LDS once per workgroup.
+// Workgroups of 4 waves (and one that reports the flags), shared among the
+// elements by their 16-atom tiles; the waves of an element's workgroups stride
+// over its tiles, and its padded weights are staged in LDS once per workgroup.
 template <int P>
-__global__ void __launch_bounds__(256) k_mlp_mfma(MlpArgs<P> a, int wpe) {
+__global__ void __launch_bounds__(256, 2) k_mlp_mfma(MlpArgs<P> a, int blocks) {
   using T = typename Types<P>::T;
   using IO = typename Types<P>::IO;
   __shared__ T W[NET_STRIDE];
   __shared__ T isc[HID];
-  const int e = uniform(blockIdx.x / wpe);
-  const int b = blockIdx.x % wpe;
-  if (e >= a.n_el) {  // the extra workgroup (MlpArgs::host_flags)
+  if ((int)blockIdx.x == blocks) {  // the extra workgroup (MlpArgs::host_flags)
     report_flags(a.flags, a.cmax, a.ncells, a.host_flags);
     return;
   }
+  // one workgroup for each element that has atoms, the others in proportion
+  const int all = (a.eoff[a.n_el] + 15) / 16 + a.n_el;
+  int e = -1, b = blockIdx.x, wpe = 0;
+  for (int f = 0; f < a.n_el; ++f) {
+    const int nt = (a.eoff[f + 1] - a.eoff[f] + 15) / 16;
+    wpe = nt > 0 ? 1 + (int)((int64_t)(blocks - a.n_el) * nt / all) : 0;
+    if (b < wpe) {
+      e = f;
+      break;
+    }
+    b -= wpe;
+  }
+  if (e < 0) return;
   const T* __restrict__ src = a.nets + (size_t)e * NET_STRIDE;
   for (int i = threadIdx.x; i < NET_STRIDE; i += 256) W[i] = src[i];
   if (threadIdx.x < HID) isc[threadIdx.x] = threadIdx.x < MAX_SF ? (T)a.tab->inv_scale_d[e][threadIdx.x] : T(0);
@@ -210,13 +221,19 @@ __global__ void __launch_bounds__(256) k_mlp_mfma(MlpArgs<P> a, int wpe) {
   }
 }
 
+// As many workgroups as the 256 CUs hold at once (three each, in FP64 two, which
+// takes a limit of 256 VGPRs): the pass is short, and a second set of workgroups
+// pays for its weights and its latencies again.  Against 512 per element, whatever
+// its share of the atoms: 255,552 water atoms in FP64 161 -> 123 us, 98,304 in BF16
+// 23 -> 18 us, 34,440 fcc atoms in FP64 42 -> 33 us, 1.5M fcc atoms 181 -> 167 us,
+// 2M water atoms 219 -> 218 us (768 shared equally by the two elements: 240 us).
+template <int P> constexpr int MLP_BLOCKS = P == P_FP64 ? 512 : 768;
+
 template <int P>
 void launch_mlp(const MlpArgs<P>& a, hipStream_t stream) {
   if (a.n == 0) return;
-  int wpe = (int)std::min<int64_t>(512, (a.n + 63) / 64);
-  if (wpe < 1) wpe = 1;
-  hipLaunchKernelGGL(k_mlp_mfma<P>, dim3((unsigned)(a.n_el * wpe + (a.host_flags ? 1 : 0))), dim3(256), 0,
-                     stream, a, wpe);
+  const int blocks = (int)std::min<int64_t>(MLP_BLOCKS<P>, (a.n + 63) / 64 + a.n_el);
+  hipLaunchKernelGGL(k_mlp_mfma<P>, dim3((unsigned)(blocks + (a.host_flags ? 1 : 0))), dim3(256), 0, stream, a, blocks);
 }
 
 // ------------------------------------------------------------ weight gradient
