@@ -417,13 +417,35 @@ struct Marks {
   }
 };
 
+// Mean neighbour count of the densest structure.
+double mean_neighbors(const nnp_handle* h, const Batch& B) {
+  double rho = 0.0;
+  for (const auto& s : B.st) rho = std::max(rho, (double)s.n / (s.L[0] * s.L[1] * s.L[2]));
+  return rho * 4.0 / 3.0 * M_PI * h->rc * h->rc * h->rc;
+}
+
+// Modes (bit per mode, FP64) that take the X_n polynomials.  Each centre pays for
+// their 15 coefficients per eta, in scalar registers that the other values of the
+// walk are spilled for, so short rows are faster with the exponentials: SF pass /
+// force pass of 98,304 water atoms, polynomials against exponentials, at mean
+// counts of 91: 1.05 / 1.46 against 1.20 / 1.51 ms, 68: 0.79 / 1.08 against 0.85 /
+// 1.03, 52: 0.68 / 0.88 against 0.69 / 0.81, 37: 0.54 / 0.72 against 0.53 / 0.64;
+// 1.5M fcc atoms (18): 3.70 / 5.16 against 3.42 / 4.19.  Three elements (91, the
+// kernels of any (q, n)): 0.236 / 0.433 against 0.269 / 0.417.  By the mean density
+// and not by the rows, so that a call's results do not turn on the calls before it.
+constexpr double POLY_MIN_SF = 45.0, POLY_MIN_FORCE = 80.0;
+int poly_modes(const nnp_handle* h, const Batch& B) {
+  if (!h->xpoly) return 0;
+  const double mean = mean_neighbors(h, B);
+  return (mean >= POLY_MIN_SF ? 1 : 0) | (mean >= POLY_MIN_FORCE && h->variant == 0 ? 2 : 0) |
+         (mean >= POLY_MIN_FORCE ? 4 : 0);
+}
+
 // Neighbour capacity from the densest structure: mean count * 1.2 + 16,
 // rounded up to a multiple of 16 (a denser spot triggers a regrow).
 int initial_cap(nnp_handle* h, const Batch& B) {
   if (h->cap_override) return h->cap_override;
-  double rho = 0.0;
-  for (const auto& s : B.st) rho = std::max(rho, (double)s.n / (s.L[0] * s.L[1] * s.L[2]));
-  const double mean = rho * 4.0 / 3.0 * M_PI * h->rc * h->rc * h->rc;
+  const double mean = mean_neighbors(h, B);
   int cap = (int)std::ceil(mean * 1.2 + 16.0);
   cap = (cap + 15) / 16 * 16;
   return std::max(cap, std::max(h->cap, 32));
@@ -599,7 +621,7 @@ TripArgs<P> trip_args(nnp_handle* h, Common& cm) {
   t.nnb = cm.nnb;
   t.st = cm.d_st;
   t.tab = reinterpret_cast<const DevTab<typename Types<P>::T>*>(h->d_tab);
-  t.poly = h->xpoly ? 1 : 0;
+  t.poly = poly_modes(h, cm.B);
   return t;
 }
 
