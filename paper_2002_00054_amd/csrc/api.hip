@@ -936,7 +936,7 @@ nnp_status evaluated(nnp_handle* h, Marks& mk, double* energy_host, bool keep, b
 // networks and dE/dG, forces, outputs in the caller's order and the energies.
 // ahead: launches the passes behind a build whose flags the host has not seen
 // (may_run_ahead) and leaves the rest to the caller; the network pass reports the
-// flags, with flags[2] the largest of cmax[0 .. cells) and itself, and without a
+// flags, with flags[2] the largest of cmax[0 .. cells), and without a
 // host energy h->reported is recorded behind it.  (Behind the build, with a
 // reduction of cmax of its own, the host could go on earlier, but the launch costs
 // more: 32-structure training step 1,003 -> 1,033 us, 12,288-atom MD 2.60 -> 2.63 ms.)
@@ -1134,42 +1134,24 @@ nnp_status forward_skin(nnp_handle* h, int64_t n, const void* pos_v, const int32
       mk.mark("regather");
     }
     if ((st = bind_neighbors<T>(h, cm))) return st;
-    const bool ahead = attempt == 0 && may_run_ahead<P>(h, 0, 1, n, NNP_LIST_PADDED);
-    if (ahead) h->lcap = cm.bin.clip = std::min(h->lcap_next, h->cap);
-    const int lcap = h->lcap;
     launch_refresh<T>(cm.bin, snbr, snnb, h->scap, h->rc, h->cap, reinterpret_cast<typename Vec4<T>::type*>(cm.nbr),
                       cm.nnb, stream);
-    cm.bin.clip = INT_MAX;
-    if (ahead) {
-      mk.mark("neighbors");
-      if ((st = evaluate<P>(h, cm, mk, bufs, 1, pos, types, energies_dev, nullptr, nullptr, f_v, stream, false, true)))
-        return st;
-      NNP_HIP(h, hipEventSynchronize(h->reported));
-    } else {
-      NNP_HIP(h, hipMemcpyAsync(h->h_flags, cm.bin.flags, 4 * sizeof(int), hipMemcpyDeviceToHost, stream));
-      NNP_HIP(h, hipStreamSynchronize(stream));
-    }
+    // The host waits here: a list that has expired, every few steps with a small
+    // skin, would waste the passes launched ahead (skin 0.5 A at 12,288 atoms:
+    // 0.53 ms per step).
+    NNP_HIP(h, hipMemcpyAsync(h->h_flags, cm.bin.flags, 4 * sizeof(int), hipMemcpyDeviceToHost, stream));
+    NNP_HIP(h, hipStreamSynchronize(stream));
     if (h->h_flags[0] & 2) return fail(h, NNP_E_ARG, "non-finite atom position (NaN or infinity)");
     if (h->h_flags[0] & 4) {  // an atom moved more than skin/2: new sort and skin list
-      if (ahead) mk.restart();
       h->skin_ok = false;
       continue;
     }
     if (h->h_flags[1] > h->cap) {
       const int nc = (int)std::ceil(h->h_flags[1] * 1.15) + 8;
       h->cap = (nc + 15) / 16 * 16;
-      if (ahead) mk.restart();
       continue;  // the next round re-gathers (unchanged) and refreshes into the larger rows
     }
     set_lcap(h, cm.layout);
-    if (ahead && h->lcap <= lcap) {
-      h->lcap = lcap;
-      return evaluated(h, mk, nullptr, false, false, stream);
-    }
-    if (ahead) {  // a row was cut: refresh again
-      mk.restart();
-      continue;
-    }
     mk.mark("neighbors");
     return evaluate<P>(h, cm, mk, bufs, 1, pos, types, energies_dev, nullptr, nullptr, f_v, stream, false);
   }

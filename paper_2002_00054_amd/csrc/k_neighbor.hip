@@ -647,7 +647,7 @@ __global__ void __launch_bounds__(256) k_regather(int64_t n, const TIn* __restri
 template <class E>
 __global__ void __launch_bounds__(256) k_refresh(int64_t n, int n_el, const double4* __restrict__ pos4,
                                                  const DevStruct* __restrict__ st, const int* __restrict__ snbr,
-                                                 const int4* __restrict__ snnb, int scap, double rc2, int cap, int clip,
+                                                 const int4* __restrict__ snnb, int scap, double rc2, int cap,
                                                  E* __restrict__ nbr, int4* __restrict__ nnb,
                                                  int* __restrict__ flags) {
   __shared__ int red[4];
@@ -682,10 +682,10 @@ __global__ void __launch_bounds__(256) k_refresh(int64_t n, int n_el, const doub
         }
         const unsigned long long msk = __builtin_amdgcn_ballot_w64(pass);
         const int rank = tot + lanes_below(msk);
-        if (pass && rank < clip) row[rank] = make_entry_as<E>(dx, dy, dz, j);
+        if (pass && rank < cap) row[rank] = make_entry_as<E>(dx, dy, dz, j);
         tot += __popcll(msk);
       }
-      kept[f] = min(tot, clip) - min(before, clip);
+      kept[f] = min(tot, cap) - min(before, cap);
       so = end;
     }
     if (lane == 0) nnb[c] = make_int4(kept[0], kept[1], kept[2], kept[3]);
@@ -903,7 +903,7 @@ void launch_refresh(const BinArgs& a, const int* snbr, const int4* snnb, int sca
   if (a.n == 0) return;
   const unsigned g = (unsigned)std::min<int64_t>((a.n + 3) / 4, 16384);
   hipLaunchKernelGGL(k_refresh<typename Vec4<T>::type>, dim3(g), dim3(256), 0, stream, a.n, a.n_el, a.pos4, a.st,
-                     snbr, snnb, scap, rc * rc, cap, std::min(cap, a.clip), nbr, nnb, a.flags);
+                     snbr, snnb, scap, rc * rc, cap, nbr, nnb, a.flags);
 }
 template void launch_refresh<float>(const BinArgs&, const int*, const int4*, int, double, int, float4*, int4*,
                                     hipStream_t);
