@@ -260,6 +260,7 @@ DevTab<T> convert_tab(const DevTab<double>& s) {
   for (int e = 0; e < MAX_EL; ++e) t.n_sf[e] = s.n_sf[e];
   t.rc2 = (T)s.rc2;
   t.inv_rc2 = (T)s.inv_rc2;
+  t.inv_rc2_lo = (T)s.inv_rc2_lo;
   for (int e = 0; e < MAX_EL; ++e) {
     for (int f = 0; f < MAX_EL; ++f) {
       t.rad_cnt[e][f] = s.rad_cnt[e][f];
@@ -1381,25 +1382,27 @@ nnp_status md_run(nnp_handle* h, int64_t n, void* pos_v, void* vel_v, void* f_v,
 
 // --------------------------------------------------------------- create
 // Interpolates X(t) = (1 + cos(pi sqrt t)) / 2 e^{-b t} at the Chebyshev points
-// of [0, 1] (Newton's divided differences, then the monomial basis in t - 1/2,
+// of [0, 1] (Newton's divided differences, then the monomial basis in t' - 1/2,
 // in long double) to degree DEG and returns the largest error of the rounded
-// coefficients' polynomial on a fine grid.  At b = eta rc^2 = 1.08 (the water
+// coefficients' polynomial on a fine grid.  t' = t / stretch = r^2 inv_rc2 is what the
+// kernels form of r^2, with the rounding of 1 / rc^2 in it: taken for t it would move
+// every term the same way.  At b = eta rc^2 = 1.08 (the water
 // table's larger eta) degree 14 is within 5e-17, and it passes XP_MAX_ERROR
 // near b = 1.35; degree 10 is enough below b = 0.04.  The exponential path's
-// cutoff polynomial alone is within 1.4e-15.  (Powers of t - 1/2, not of t: the
-// rounding of their coefficients is half as large and, unlike with powers of t,
-// leaves no common sign, which summed energies would show.)
+// cutoff polynomial alone is within 1e-16.  (Powers of t' - 1/2, not of t': the
+// rounding of their coefficients is half as large and leaves less than 1e-16 of common
+// error in an SF's sum over a box, where powers of t' had up to 8e-16.)
 constexpr double XP_MAX_ERROR = 3e-16, XP_LOW_ERROR = 1.2e-16;
 template <int DEG>
-double fit_xpoly(double b, double* c) {
+double fit_xpoly(long double b, long double stretch, double* c) {
   using L = long double;
   const L pi = 3.14159265358979323846264338327950288L;
-  auto X = [&](L t) { return (1.0L + cosl(pi * sqrtl(t))) / 2.0L * expl(-(L)b * t); };
+  auto X = [&](L t) { return (1.0L + cosl(pi * sqrtl(t))) / 2.0L * expl(-b * t); };
   constexpr int N = DEG + 1;
   L t[N], d[N], p[N] = {};  // t: the points, less 1/2
   for (int i = 0; i < N; ++i) {
     t[i] = cosl(pi * (i + 0.5L) / N) / 2.0L;
-    d[i] = X(t[i] + 0.5L);
+    d[i] = X(stretch * (t[i] + 0.5L));
   }
   for (int k = 1; k < N; ++k)
     for (int i = N - 1; i >= k; --i) d[i] = (d[i] - d[i - 1]) / (t[i] - t[i - k]);
@@ -1414,7 +1417,7 @@ double fit_xpoly(double b, double* c) {
     const L x = g / 200.0L;
     L v = c[N - 1];
     for (int i = N - 2; i >= 0; --i) v = v * (x - 0.5L) + (L)c[i];
-    const L e = fabsl(v - X(x));
+    const L e = fabsl(v - X(stretch * x));
     if (!(e <= worst)) worst = e;  // NaN too
   }
   return (double)worst;
@@ -1498,6 +1501,11 @@ nnp_status build_table(nnp_handle* h, int n_el, int n_sf, const nnp_sf* sf, cons
       t.ang_out[e][cls][q] = k;
     }
   }
+  const long double rc2 = (long double)h->rc * h->rc;
+  t.rc2 = h->rc * h->rc;
+  t.inv_rc2 = (double)(1 / rc2);
+  t.inv_rc2_lo = std::isfinite(t.inv_rc2) ? (double)(1 / rc2 - t.inv_rc2) : 0.0;
+  const long double rc2_rounded = 1 / (long double)t.inv_rc2;
   int ne_max = 1;
   h->xpoly = h->prec == NNP_FP64;
   for (int e = 0; e < n_el; ++e) {
@@ -1515,17 +1523,15 @@ nnp_status build_table(nnp_handle* h, int n_el, int n_sf, const nnp_sf* sf, cons
             t.xhigh[e][x] = t.xhigh[f][y];
           }
       if (known) continue;
-      const double b = etas[e][x] * h->rc * h->rc;
-      t.xhigh[e][x] = fit_xpoly<XP_LOW>(b, t.xpoly[e][x]) <= XP_LOW_ERROR ? 0 : 1;
-      if (t.xhigh[e][x] && !(fit_xpoly<XP_DEG>(b, t.xpoly[e][x]) <= XP_MAX_ERROR)) h->xpoly = false;
+      const long double b = etas[e][x] * rc2;
+      t.xhigh[e][x] = fit_xpoly<XP_LOW>(b, rc2_rounded / rc2, t.xpoly[e][x]) <= XP_LOW_ERROR ? 0 : 1;
+      if (t.xhigh[e][x] && !(fit_xpoly<XP_DEG>(b, rc2_rounded / rc2, t.xpoly[e][x]) <= XP_MAX_ERROR)) h->xpoly = false;
     }
     ne_max = std::max(ne_max, t.n_eta[e]);
   }
   if (ne_max > 2) h->variant = 2;
   else if ((qn_mask & ~QN_WATER) == 0) h->variant = 0;
   else h->variant = 1;
-  t.rc2 = h->rc * h->rc;
-  t.inv_rc2 = 1.0 / t.rc2;
   h->n_sf = count;
   // networks
   h->sizes.clear();

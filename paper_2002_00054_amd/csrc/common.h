@@ -64,7 +64,7 @@ struct DevTab {
   int n_el;
   int n_sf[MAX_EL];
   T rc2;                               // rc^2
-  T inv_rc2;                           // 1 / rc^2
+  T inv_rc2, inv_rc2_lo;               // 1 / rc^2, and what its rounding leaves of it (FP64 SF passes)
   // radial SFs, per (centre e, neighbour element f)
   int rad_cnt[MAX_EL][MAX_EL];
   T rad_eta[MAX_EL][MAX_EL][MAX_RAD];
@@ -250,17 +250,20 @@ __device__ inline float rsqrt_t(float s) { return __builtin_amdgcn_rsqf(s); }
 
 // Cutoff polynomial in t = r^2/rc^2 per arithmetic type: interpolants of
 // fc = (1 + cos(pi sqrt(t)))/2 at the Chebyshev points (gen_cutoff.py).  FP64:
-// degree 10 in powers of t - 1/2, max error 4e-17 (fc) and 4e-15 (dfc/dt)
-// before rounding.  FP32: degree 6 in powers of t, max error 5.5e-9, below
+// degree 10 in powers of t - 1/2, max error 5e-17 (fc) and 4e-15 (dfc/dt)
+// before rounding, rounded for the least mean error.  FP32: degree 6 in powers of t, max error 5.5e-9, below
 // FP32 rounding.  Both are several terms shorter than the Taylor series of the
 // same accuracy.
 template <class T> struct FcPoly;
 template <> struct FcPoly<double> {
   static constexpr int D = 10;
   __device__ static double variable(double s, double inv_rc2) { return __builtin_fma(s, inv_rc2, -0.5); }
+  __device__ static double variable(double s, double inv_rc2, double inv_rc2_lo) {
+    return __builtin_fma(s, inv_rc2_lo, variable(s, inv_rc2));
+  }
   static constexpr double a(int n) {
-    constexpr double c[11] = {0.1971500664605933,      -0.88379293731319197,   1.1891487278891328,
-                              -0.46225817257593987,    0.088804902456443971,   -0.010269231077289678,
+    constexpr double c[11] = {0.19715006646059327,     -0.88379293731319197,   1.1891487278891331,
+                              -0.46225817257593999,    0.088804902456443971,   -0.010269231077289678,
                               0.00079602567959765269,  -4.4311202098710064e-05, 1.8587616141233574e-06,
                               -6.0917656138878952e-08, 1.6020207321886072e-09};
     return c[n];
@@ -269,6 +272,7 @@ template <> struct FcPoly<double> {
 template <> struct FcPoly<float> {
   static constexpr int D = 6;
   __device__ static float variable(float s, float inv_rc2) { return s * inv_rc2; }
+  __device__ static float variable(float s, float inv_rc2, float) { return s * inv_rc2; }
   static constexpr double a(int n) {
     constexpr double c[7] = {0.99999999447228860, -2.4674005583220304, 2.0293473727609408, -0.66757901115278839,
                              0.11751451131309654, -0.012679142877827992, 0.00079683910699860207};
@@ -278,18 +282,27 @@ template <> struct FcPoly<float> {
 
 // Cosine cutoff as a polynomial in s = r^2 with compile-time coefficients
 // (no square root or cosine per evaluation); exactly 0 for s >= rc^2 unless
-// the caller already knows s < rc^2 (the *_in variants).
-template <class T>
+// the caller already knows s < rc^2 (the *_in variants).  LOW (the SF passes; FP64):
+// t takes the low part of 1 / rc^2 as well.  The rounding of 1 / rc^2 alone moves every
+// fc the same way, by 8e-17 of their mean at rc = 6, and energies are small differences
+// of sums of them: total energy of 375 water atoms against extended precision, in
+// parts of 1e-14, 5 without and 1 with it.  Forces do not cancel so, and the value's two
+// scalar registers cost the force pass of the wide functions 3 %.
+template <class T, bool LOW = false>
 struct Cutoff {
   static constexpr int D = FcPoly<T>::D;
-  T rc2, inv_rc2;
+  T rc2, inv_rc2, inv_rc2_lo;
   __device__ inline void load(const DevTab<T>* tab) {
     rc2 = tab->rc2;
     inv_rc2 = tab->inv_rc2;
+    if (LOW) inv_rc2_lo = tab->inv_rc2_lo;
+  }
+  __device__ inline T variable(T s) const {
+    return LOW ? FcPoly<T>::variable(s, inv_rc2, inv_rc2_lo) : FcPoly<T>::variable(s, inv_rc2);
   }
   // fc and dfc/ds at s = r^2, for s < rc^2.
   __device__ inline void eval_in(T s, T& fc, T& dfc_ds) const {
-    const T t = FcPoly<T>::variable(s, inv_rc2);
+    const T t = variable(s);
     T f = T(FcPoly<T>::a(D)), g = T(D * FcPoly<T>::a(D));
 #pragma unroll
     for (int n = D - 1; n >= 1; --n) {
@@ -306,7 +319,7 @@ struct Cutoff {
     dfc_ds = in ? dfc_ds : T(0);
   }
   __device__ inline T value_in(T s) const {
-    const T t = FcPoly<T>::variable(s, inv_rc2);
+    const T t = variable(s);
     T f = T(FcPoly<T>::a(D));
 #pragma unroll
     for (int n = D - 1; n >= 0; --n) f = f * t + T(FcPoly<T>::a(n));

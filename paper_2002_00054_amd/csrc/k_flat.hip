@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(FLAT) k_flat_sf(TripArgs<P> a) {
   const int64_t c = xcd_remap(blockIdx.x, gridDim.x) * FLAT + lane;
   if (c >= a.n) return;  // no workgroup barrier below
   const DevTab<T>* __restrict__ tab = a.tab;
-  Cutoff<T> cut;
+  Cutoff<T, true> cut;
   cut.load(tab);
   const T rc2 = tab->rc2;
   const int n_el = tab->n_el;

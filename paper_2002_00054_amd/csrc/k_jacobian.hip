@@ -63,7 +63,7 @@ __global__ void __launch_bounds__(256) k_jac(JacArgs<P> a) {
   Acc* gsum = reinterpret_cast<Acc*>(aux + lcap);
 
   const DevTab<T>* __restrict__ tab = a.tab;
-  Cutoff<T> cut;
+  Cutoff<T, true> cut;
   cut.load(tab);
   const T rc2 = tab->rc2;
   const double4 pc = a.pos4[c];
