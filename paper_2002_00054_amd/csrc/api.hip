@@ -74,7 +74,7 @@ struct nnp_handle {
   // workspace
   std::map<std::string, nnp::DevBuf> ws;
   int cap = 0;                          // neighbour slots per atom
-  int lcap = 0;                         // at least the most neighbours of any atom in the last build, rounded up
+  int lcap = 0;                         // the most neighbours of any atom in the last build, rounded up
   int lcap_next = 0;                    // capacity to launch the next call's passes with (0: none yet),
   int lcap_lower = 0;                   // calls since one needed it, and the most that these needed
   int lcap_recent = 0;
@@ -646,7 +646,7 @@ void set_lcap(nnp_handle* h, int layout) {
 
 // Waits for the flags of a neighbour build; returns 1 if the neighbour
 // capacity overflowed (rebuild), 0 if all is well (lcap
-// then bounds every atom's count), <0 on error.  ahead: the passes are launched
+// is then the largest count, rounded up), <0 on error.  ahead: the passes are launched
 // already, with rows cut at h->lcap; 1 too if a row outgrew it.
 // event: wait for h->reported, not for the whole stream.
 int check_flags(nnp_handle* h, hipStream_t stream, Common& cm, nnp_status* st, bool ahead = false, bool event = false) {
@@ -670,12 +670,9 @@ int check_flags(nnp_handle* h, hipStream_t stream, Common& cm, nnp_status* st, b
     h->cap = (nc + 15) / 16 * 16;
     return 1;
   }
-  const int was = ahead ? h->lcap : 0;
-  set_lcap(h, cm.layout);
-  if (!ahead) return 0;
-  if (h->lcap > was) return 1;
-  h->lcap = was;  // what this call's rows and masks are laid out for
-  return 0;
+  const int was = h->lcap;
+  set_lcap(h, cm.layout);  // exact from here on: a gradient of this batch takes its level from its own rows
+  return ahead && h->lcap > was ? 1 : 0;
 }
 
 // Level of the pair passes of modes mode_a and mode_b (0 SF, 1 force, 2
@@ -713,7 +710,8 @@ constexpr int64_t AHEAD_MAX_ATOMS = 131072;
 
 // The wave level of the passes of modes mode_a and mode_b may be launched ahead:
 // it stages lcap_next rows in the LDS at the number of waves that the exact
-// capacity, which is no larger, would take too.
+// capacity, which is no larger, would take too.  (A gradient call on the same batch
+// chooses its level by the exact one.)
 template <int P>
 bool may_run_ahead(const nnp_handle* h, int mode_a, int mode_b, int64_t n, int layout) {
   if (n == 0 || n > AHEAD_MAX_ATOMS || h->lcap_next == 0 || layout == NNP_LIST_COMPACT) return false;
