@@ -850,7 +850,10 @@ bool fwd_maybe_reusable(nnp_handle* h, Common& cm, const IO* pos, const int32_t*
   if ((*st = ensure_t(h, "jpos", (size_t)std::max<int64_t>(cm.B.n, 1) * 3, &sp))) return false;
   if ((*st = ensure_t(h, "jtypes", (size_t)std::max<int64_t>(cm.B.n, 1), &stp))) return false;
   if ((*st = prepare<IO>(h, cm, pos, types, stream, false))) return false;
-  // flags[3] is 0 here: the sort cleared it, and a comparison that sets it ends fwd_valid
+  // flags[3] is 0 here: the sort cleared it, and a comparison that may have set it ends
+  // fwd_valid, until fwd_same has seen that it did not (a call that fails before that
+  // must not leave a closed gate to the next one)
+  h->fwd_valid = false;
   h->h_flags[3] = 0;
   launch_same_inputs<IO>(cm.B.n, pos, sp, types, stp, cm.bin.flags + 3, h->h_flags_dev + 3, stream);
   const hipError_t e = hipEventRecord(h->reported, stream);
@@ -870,8 +873,7 @@ bool fwd_same(nnp_handle* h, nnp_status* st) {
     *st = fail(h, NNP_E_HIP, std::string("readback: ") + hipGetErrorString(e));
     return false;
   }
-  if (h->h_flags[3] != 0) h->fwd_valid = false;
-  return h->fwd_valid;
+  return h->fwd_valid = h->h_flags[3] == 0;
 }
 
 // Buffers of one forward evaluation (sorted order unless stated).

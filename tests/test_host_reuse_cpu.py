@@ -1,0 +1,85 @@
+"""What a handle keeps between calls when a call fails half-way, on the CPU: the built
+library over a stand-in for the HIP runtime (fake_hip.cpp), in a process of its own.
+
+nnp_backward reuses the last batch forward if its inputs are the same, which a kernel
+compares while the gradient's kernels are already launched behind a gate.  After a call
+that failed between the two, a gradient on the first inputs is written, whether it
+reuses the forward or repeats it."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PROGRAM = r"""
+import ctypes as C, sys, types
+sys.path[:0] = [sys.argv[2], sys.argv[3]]
+sys.modules["torch"] = types.ModuleType("torch")  # would load the real runtime
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+fake.fake_fail_launch.argtypes = fake.fake_launches.argtypes = [C.c_char_p]
+fake.fake_launches.restype = C.c_long
+import numpy as np
+from paper_2002_00054_amd import nnp, synth
+from common import water_potential
+L = nnp.load_library()
+pot = nnp.Potential(*water_potential(), precision="fp64")
+
+class Batch:
+    def __init__(self, side, seed):
+        b = synth.water_box(side, seed)
+        self.n, self.pos, self.types = b.n_atoms, b.pos.copy(), b.types.astype(np.int32)
+        self.offs, self.box = (C.c_int64 * 2)(0, b.n_atoms), (C.c_double * 3)(*b.box)
+    def args(self):
+        return (pot._h, 1, self.offs, self.pos.ctypes.data, self.types.ctypes.data, self.box)
+    def forward(self):
+        e, ei, f = np.zeros(1), np.zeros(self.n), np.zeros((self.n, 3))
+        return L.nnp_compute_batch(*self.args(), e.ctypes.data, ei.ctypes.data, f.ctypes.data, None)
+    def backward(self):
+        g, dE, dF = np.zeros(pot.n_params), np.ones(1), np.ones((self.n, 3))
+        st = L.nnp_backward(*self.args(), dE.ctypes.data, dF.ctypes.data, g.ctypes.data, None)
+        return st, bool((g == 1.0).all())
+
+a, other, larger = Batch(5, 1), Batch(5, 2), Batch(6, 3)
+sorts = lambda: fake.fake_launches(b"k_sort_small")
+assert a.forward() == 0 and a.forward() == 0
+n = sorts()
+assert a.backward() == (0, True) and sorts() == n  # the forward is reused
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    from paper_2002_00054_amd import build, nnp
+
+    if not os.path.exists(nnp.LIB_PATH):
+        build.build(verbose=False)
+    so = str(tmp_path_factory.mktemp("fake") / "libamdhip64.so.7")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-Wl,-soname,libamdhip64.so.7", "-o", so,
+                    os.path.join(HERE, "fake_hip.cpp")], check=True)
+    return so
+
+
+def _run(fake, more):
+    r = subprocess.run([sys.executable, "-c", PROGRAM + more, fake, os.path.dirname(HERE), HERE], capture_output=True,
+                       text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-3000:]
+
+
+FAILED = """
+assert other.backward()[0] == nnp_error
+n = sorts()
+st, written = a.backward()
+assert st == 0 and written, (st, written)
+assert a.backward() == (0, True)
+"""
+
+
+@pytest.mark.parametrize("kernel", ["k_triplet", "k_wgrad_final"])
+def test_a_launch_fails_behind_the_comparison(fake, kernel):
+    _run(fake, "nnp_error = -4\nfake.fake_fail_launch(b'%s')" % kernel + FAILED)
+
+
+def test_the_wait_for_the_comparison_fails(fake):
+    _run(fake, "nnp_error = -4\nfake.fake_fail_event(0)" + FAILED)
