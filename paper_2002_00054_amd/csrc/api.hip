@@ -477,6 +477,12 @@ nnp_status prepare(nnp_handle* h, Common& cm, const IO* pos, const int32_t* type
   const int64_t n = B.n;
   const int nkeys = h->n_el * B.total_cells;
   nnp_status st;
+  if (sort) {  // before any buffer is replaced by a larger one
+    h->fwd_valid = false;  // the sorted order, neighbour list, G~ and J store are about to change
+    h->fwd_pm = nullptr;   // and so are the pair-test masks
+    h->fwd_pm_stride = 0;
+    h->skin_ok = false;    // and the Verlet-skin list with them
+  }
   const size_t nst = B.st.size(), nso = B.soff.size(), nch = B.chunk_lo.size(), nsc = B.struct_chunk.size();
   // The batch description goes up in one copy: its five arrays are packed,
   // 16-byte aligned, into one pinned staging block and one device block.
@@ -529,10 +535,6 @@ nnp_status prepare(nnp_handle* h, Common& cm, const IO* pos, const int32_t* type
   if ((st = ensure_t(h, "eoff", MAX_EL + 1, &a.eoff))) return st;
   if ((st = ensure_t(h, "flags", N_FLAGS, &a.flags))) return st;
   if (!sort) return NNP_OK;
-  h->fwd_valid = false;  // the sorted order, neighbour list, G~ and J store are about to change
-  h->fwd_pm = nullptr;   // and so are the pair-test masks
-  h->fwd_pm_stride = 0;
-  h->skin_ok = false;    // and the Verlet-skin list with them
   launch_bin_sort<IO>(a, pos, stream);
   return NNP_OK;
 }
@@ -831,14 +833,14 @@ nnp_status fwd_remember(nnp_handle* h, const Common& cm, const IO* pos, const in
 }
 
 // True if the workspace may still hold the forward results of these inputs
-// (same batch layout and capacity): it does if h_flags[3] is 0 once h->reported
+// (kept: it holds some; same batch layout and capacity): it does if h_flags[3] is 0 once h->reported
 // has been reached (bitwise equal positions and types, compared on the device,
 // where flags[3] says the same).  Binds the sorted-order buffers of cm then.
 template <class IO>
-bool fwd_maybe_reusable(nnp_handle* h, Common& cm, const IO* pos, const int32_t* types, hipStream_t stream,
+bool fwd_maybe_reusable(nnp_handle* h, bool kept, Common& cm, const IO* pos, const int32_t* types, hipStream_t stream,
                         nnp_status* st) {
   *st = NNP_OK;
-  if (!h->fwd_valid || h->fwd_cap != h->cap) return false;
+  if (!kept || h->fwd_cap != h->cap) return false;
   if (h->fwd_offs.size() != cm.B.soff.size() ||
       !std::equal(h->fwd_offs.begin(), h->fwd_offs.end(), cm.B.soff.begin()))
     return false;
@@ -850,10 +852,9 @@ bool fwd_maybe_reusable(nnp_handle* h, Common& cm, const IO* pos, const int32_t*
   if ((*st = ensure_t(h, "jpos", (size_t)std::max<int64_t>(cm.B.n, 1) * 3, &sp))) return false;
   if ((*st = ensure_t(h, "jtypes", (size_t)std::max<int64_t>(cm.B.n, 1), &stp))) return false;
   if ((*st = prepare<IO>(h, cm, pos, types, stream, false))) return false;
-  // flags[3] is 0 here: the sort cleared it, and a comparison that may have set it ends
-  // fwd_valid, until fwd_same has seen that it did not (a call that fails before that
-  // must not leave a closed gate to the next one)
-  h->fwd_valid = false;
+  // flags[3] is 0 here: the sort cleared it, and a comparison that may have set it has
+  // ended fwd_valid, until fwd_same has seen that it did not (a call that fails before
+  // that must not leave a closed gate to the next one)
   h->h_flags[3] = 0;
   launch_same_inputs<IO>(cm.B.n, pos, sp, types, stp, cm.bin.flags + 3, h->h_flags_dev + 3, stream);
   const hipError_t e = hipEventRecord(h->reported, stream);
@@ -1175,6 +1176,9 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
   h->cap = initial_cap(h, cm.B);
   Marks mk(h, stream);
   (void)hipGetLastError();
+  // given back by fwd_same: a buffer below may be replaced by a larger one, and the call fail after that
+  const bool kept = h->fwd_valid;
+  h->fwd_valid = false;
   IO *G, *V, *delta;
   double* part;
   const int64_t n1 = std::max<int64_t>(n, 1);
@@ -1245,7 +1249,7 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
     mk.mark("wgrad");
     return check_launch(h, "backward");
   };
-  bool ready = fwd_maybe_reusable<IO>(h, cm, pos, types, stream, &st);
+  bool ready = fwd_maybe_reusable<IO>(h, kept, cm, pos, types, stream, &st);
   if (st) return st;
   bool launched = false;
   if (ready) {

@@ -83,3 +83,22 @@ def test_a_launch_fails_behind_the_comparison(fake, kernel):
 
 def test_the_wait_for_the_comparison_fails(fake):
     _run(fake, "nnp_error = -4\nfake.fake_fail_event(0)" + FAILED)
+
+
+@pytest.mark.parametrize("call", ["forward", "backward"])
+def test_memory_runs_out_for_a_larger_batch(fake, call):
+    """Whichever of its allocations fails: buffers before it have replaced the kept ones."""
+    _run(fake, """
+for k in range(40):
+    assert a.forward() == 0
+    n = sorts()
+    assert a.backward() == (0, True) and sorts() == n
+    fake.fake_fail_malloc(k)
+    larger = Batch(6 + k % 3, 3)  # sizes in turn, so that one always needs more
+    st = larger.CALL()
+    st = st[0] if isinstance(st, tuple) else st
+    assert st in (0, -5), st
+    fake.fake_fail_malloc(-1)
+    n = sorts()
+    assert a.backward() == (0, True) and sorts() > n, (k, st)
+""".replace("CALL", call))
