@@ -403,10 +403,11 @@ struct Marks {
     if (name) h->t_names.push_back(name);
     ++k;
   }
-  void restart() {  // the stages so far are run again
-    k = 0;
-    h->t_names.clear();
-    if (h->prof) mark(nullptr);
+  // the stages after the first so many are run again: their time goes to the next one
+  void restart(int stages) {
+    if (!h->prof) return;
+    k = std::min(k, stages + 1);
+    h->t_names.resize(std::min<size_t>(h->t_names.size(), stages));
   }
   void finish() {
     if (!h->prof) return;
@@ -1059,7 +1060,7 @@ nnp_status forward(nnp_handle* h, int n_struct, const int64_t* offs, const void*
     const int r = check_flags(h, stream, cm, &st, ahead, ahead && !synced);
     if (r < 0) return st;
     if (ahead && r == 0) return evaluated(h, mk, energy_host, remember, synced, stream);
-    if (ahead) mk.restart();
+    if (ahead) mk.restart(1);  // after the sort
     if (r == 1) continue;  // a capacity grew: rebuild the neighbour list
     if (layout != NNP_LIST_PADDED) {
       bool flat = false;
@@ -1265,7 +1266,7 @@ nnp_status backward(nnp_handle* h, int n_struct, const int64_t* offs, const void
     }
     const bool same = fwd_same<IO>(h, &st);
     if (st) return st;
-    if (launched && !same) mk.restart();
+    if (launched && !same) mk.restart(0);
     launched = launched && same;
     ready = ready && same;
     if (ready && level) return level;

@@ -16,6 +16,9 @@ std::string fail_launch;  // a launch of a kernel of this name fails, once
 int fail_malloc = -1, fail_event = -1;  // this many more succeed before one fails (-1: none fails)
 int last_error = 0;
 std::map<std::string, long> launches;
+std::map<std::string, size_t> lds;  // of a kernel's last launch
+int* flags = nullptr;               // the handle's pinned flags (the one allocation of 16 bytes)
+int rows = 0;                       // longest neighbour row that a build reports
 struct Config { Dim3 g, b; size_t lds; void* s; } config;
 
 template <class X> X arg(void** a, int i) { return *static_cast<X*>(a[i]); }
@@ -26,6 +29,12 @@ extern "C" {
 void fake_fail_launch(const char* name) { fail_launch = name; }
 void fake_fail_malloc(int after) { fail_malloc = after; }
 void fake_fail_event(int after) { fail_event = after; }
+void fake_rows(int n) { rows = n; }
+size_t fake_lds(const char* name) {
+  for (auto& x : lds)
+    if (x.first.find(name) != std::string::npos) return x.second;
+  return 0;
+}
 long fake_launches(const char* name) {
   long n = 0;
   for (auto& x : launches)
@@ -44,7 +53,7 @@ int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* lds, void** s) {
   *g = config.g, *b = config.b, *lds = config.lds, *s = config.s;
   return 0;
 }
-int hipLaunchKernel(const void* f, Dim3, Dim3, void** a, size_t, void*) {
+int hipLaunchKernel(const void* f, Dim3, Dim3, void** a, size_t shared, void*) {
   const std::string& k = names[f];
   auto is = [&](const char* name) { return k.find(name) != std::string::npos; };
   if (!fail_launch.empty() && is(fail_launch.c_str())) {
@@ -52,6 +61,8 @@ int hipLaunchKernel(const void* f, Dim3, Dim3, void** a, size_t, void*) {
     return last_error = 719;
   }
   ++launches[k];
+  lds[k] = shared;
+  if (is("k_max_count") || is("k_mlp")) flags[2] = rows;
   if (is("k_sort_small")) std::memset(arg<int*>(a, 14), 0, 5 * sizeof(int));
   if (is("k_copy_inputs")) {  // FP64
     const int64_t n = arg<int64_t>(a, 0);
@@ -77,7 +88,11 @@ int hipMalloc(void** p, size_t n) {
   return (*p = std::calloc(n, 1)) ? 0 : 2;
 }
 int hipFree(void* p) { std::free(p); return 0; }
-int hipHostMalloc(void** p, size_t n, unsigned) { return (*p = std::calloc(n, 1)) ? 0 : 2; }
+int hipHostMalloc(void** p, size_t n, unsigned) {
+  *p = std::calloc(n, 1);
+  if (n == 16) flags = static_cast<int*>(*p);
+  return *p ? 0 : 2;
+}
 int hipHostFree(void* p) { std::free(p); return 0; }
 int hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return 0; }
 int hipMemcpy(void* d, const void* s, size_t n, int) { std::memcpy(d, s, n); return 0; }

@@ -1,5 +1,5 @@
-"""What a handle keeps between calls when a call fails half-way, on the CPU: the built
-library over a stand-in for the HIP runtime (fake_hip.cpp), in a process of its own.
+"""What a handle keeps between calls, on the CPU: the built library over a stand-in for
+the HIP runtime (fake_hip.cpp), in a process of its own.
 
 nnp_backward reuses the last batch forward if its inputs are the same, which a kernel
 compares while the gradient's kernels are already launched behind a gate.  After a call
@@ -102,3 +102,17 @@ for k in range(40):
     n = sorts()
     assert a.backward() == (0, True) and sorts() > n, (k, st)
 """.replace("CALL", call))
+
+
+def test_stages_of_a_call_whose_rows_outgrew_the_capacity(fake):
+    """Its passes are run again; every stage of the call is still reported, the sort too."""
+    _run(fake, """
+stages = ["bin_sort", "neighbors", "sf", "mlp", "force", "finish"]
+pot.set_profiling(True)
+for rows in (90, 90, 110):
+    fake.fake_rows(rows)
+    n = fake.fake_launches(b"k_mlp")
+    assert a.forward() == 0
+    assert list(pot.timings()) == stages, (rows, pot.timings())
+assert fake.fake_launches(b"k_mlp") == n + 2
+""")
