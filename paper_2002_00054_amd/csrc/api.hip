@@ -76,8 +76,13 @@ struct nnp_handle {
   int cap = 0;                          // neighbour slots per atom
   int lcap = 0;                         // the most neighbours of any atom in the last build, rounded up
   int lcap_next = 0;                    // capacity to launch the next call's passes with (0: none yet),
+  double lcap_mean = 0.0;               // mean neighbours of the densest batch that it was enough for,
   int lcap_lower = 0;                   // calls since one needed it, and the most that these needed
   int lcap_recent = 0;
+  double lcap_recent_mean = 0.0;
+  int ahead_wait = 0;                   // calls that do not run ahead, after one that did in vain,
+  int ahead_back = 16;                  // as many after the next such call,
+  int ahead_good = 0;                   // and calls since that ran ahead well
   hipEvent_t reported = nullptr;        // a call that launches ahead of its flags waits for this
   int cap_override = 0;
   // pinned staging for small uploads / readbacks
@@ -630,21 +635,31 @@ TripArgs<P> trip_args(nnp_handle* h, Common& cm) {
 }
 
 // Row capacity for the counts in h_flags: exact for this call's passes, and for
-// the next call's the most that one of the last calls needed (it shrinks after 16
-// calls that needed less).  Compact rows are not bounded by cap.
-void set_lcap(nnp_handle* h, int layout) {
+// the next call's the most that one of the last calls needed.  It shrinks after 16
+// calls that needed less; at once for a batch of more than AHEAD_ANY_ROWS_ATOMS whose
+// own rows are shorter by more than 16.  Compact rows are not bounded by cap.
+// The line: beyond it rows longer than needed cost occupancy, and a call that ran ahead
+// in vain more than many waits.  98,304 atoms in BF16, calls of two densities in turn
+// 1,761 us on the longer rows, 1,731 waiting where they change; one call in twenty on a
+// clustered box 1,829 us, with the shorter rows at once and waits after a miss 1,633.
+// 12,288 atoms in FP32: 295 us on the longer rows, 300 waiting.
+constexpr int64_t AHEAD_ANY_ROWS_ATOMS = 16384;
+void set_lcap(nnp_handle* h, const Batch& B, int layout) {
   h->lcap = (std::max(h->h_flags[2], 1) + 7) / 8 * 8;
   if (layout != NNP_LIST_COMPACT) h->lcap = std::min(h->lcap, h->cap);
-  if (h->lcap >= h->lcap_next) {
-    h->lcap_next = h->lcap;
-    h->lcap_lower = h->lcap_recent = 0;
-  } else {
-    h->lcap_recent = std::max(h->lcap_recent, h->lcap);
-    if (++h->lcap_lower == 16) {
-      h->lcap_next = h->lcap_recent;
-      h->lcap_lower = h->lcap_recent = 0;
-    }
+  const double mean = mean_neighbors(h, B);
+  const bool lower = h->lcap < h->lcap_next;
+  if (h->lcap <= h->lcap_next) h->lcap_mean = std::max(h->lcap_mean, mean);  // lcap_next is enough for this one too
+  if (lower) {
+    const bool first = h->lcap_lower == 0;
+    h->lcap_recent = first ? h->lcap : std::max(h->lcap_recent, h->lcap);
+    h->lcap_recent_mean = first ? mean : std::max(h->lcap_recent_mean, mean);
+    const bool at_once = B.n > AHEAD_ANY_ROWS_ATOMS && h->lcap + 16 < h->lcap_next;
+    if (++h->lcap_lower < 16 && !at_once) return;
   }
+  if (h->lcap != h->lcap_next) h->lcap_mean = lower ? h->lcap_recent_mean : mean;
+  h->lcap_next = lower ? h->lcap_recent : h->lcap;
+  h->lcap_lower = 0;
 }
 
 // Waits for the flags of a neighbour build; returns 1 if the neighbour
@@ -674,7 +689,7 @@ int check_flags(nnp_handle* h, hipStream_t stream, Common& cm, nnp_status* st, b
     return 1;
   }
   const int was = h->lcap;
-  set_lcap(h, cm.layout);  // exact from here on: a gradient of this batch takes its level from its own rows
+  set_lcap(h, cm.B, cm.layout);  // exact from here on: a gradient of this batch takes its level from its own rows
   return ahead && h->lcap > was ? 1 : 0;
 }
 
@@ -705,21 +720,32 @@ constexpr int PAIR_MASK_MIN_NEIGHBORS = 64;
 // at once, on rows cut at the capacity that the handle's last calls needed
 // (lcap_next), and look at the build's flags afterwards; where a row was cut or the
 // inputs were refused, nothing is written to the caller (Gate), and the call goes
-// on as a first call does: build, wait for the flags, launch.  That wait in the middle left the GPU idle for 12 us: water of 192 atoms
-// 97 -> 84 us, 1,029 in FP64 176 -> 163 us, 12,288 281 -> 275 us; three-element
-// 15,147 atoms 422 -> 415 us; 98,304 in BF16 1,513 -> 1,507 us.  Larger calls gain
-// less than 0.5 %, and a capacity of other inputs could cost them occupancy.
+// on as a first call does: build, wait for the flags, launch.  That wait in the middle
+// left the GPU idle for 12 us: water of 192 atoms 97 -> 84 us, 1,029 in FP64 176 -> 163
+// us, 12,288 281 -> 275 us; three-element 15,147 atoms 422 -> 415 us; 98,304 in BF16
+// 1,513 -> 1,507 us.  Larger calls gain less than 0.5 %.
 constexpr int64_t AHEAD_MAX_ATOMS = 131072;
 
 // The wave level of the passes of modes mode_a and mode_b may be launched ahead:
 // it stages lcap_next rows in the LDS at the number of waves that the exact
 // capacity, which is no larger, would take too.  (A gradient call on the same batch
-// chooses its level by the exact one.)
+// chooses its level by the exact one.)  A call that ran ahead in vain costs its passes
+// twice, so a batch denser than those that lcap_next was enough for waits for its own rows
+// (by more than a hundredth: the rows are rounded up to eight); so does a sparser one
+// that fills the machine, which would pay for the longer rows in occupancy.  What the
+// mean does not show (clustered boxes) is left to ran_ahead.
 template <int P>
-bool may_run_ahead(const nnp_handle* h, int mode_a, int mode_b, int64_t n, int layout) {
+bool may_run_ahead(nnp_handle* h, int mode_a, int mode_b, const Batch& B, int layout) {
+  const int64_t n = B.n;
   if (n == 0 || n > AHEAD_MAX_ATOMS || h->lcap_next == 0 || layout == NNP_LIST_COMPACT) return false;
   if (h->parallelism == NNP_PAR_THREAD || h->wide_flat || (P == P_BF16 && h->has_wide)) return false;
   if (P != P_BF16 && h->deriv_mode == NNP_DERIV_STORED && !h->arena_on) return false;
+  if (n > AHEAD_ANY_ROWS_ATOMS && h->ahead_wait > 0) {
+    --h->ahead_wait;
+    return false;
+  }
+  const double mean = mean_neighbors(h, B);
+  if (mean > 1.01 * h->lcap_mean || (n > AHEAD_ANY_ROWS_ATOMS && mean < 0.95 * h->lcap_mean)) return false;
   const int lcap = std::min(h->lcap_next, h->cap);
   const int w = h->has_wide                                                             ? 1
                 : h->parallelism == NNP_PAR_WAVE2 ||
@@ -727,6 +753,20 @@ bool may_run_ahead(const nnp_handle* h, int mode_a, int mode_b, int64_t n, int l
                                                                                         : 1;
   return std::max(triplet_lds_bytes<P>(mode_a, h->variant, lcap, w), triplet_lds_bytes<P>(mode_b, h->variant, lcap, w)) <=
          lds_limit();
+}
+
+// A batch that fills the machine ran ahead, in vain (missed) or not.  After one in vain
+// the next 16 calls wait, and twice as many (up to 1,024) after another one that follows
+// before as many have run well.  (Smaller ones lose 60 us by a miss and 12 by a wait.)
+void ran_ahead(nnp_handle* h, bool missed) {
+  if (missed) {
+    h->ahead_wait = h->ahead_back;
+    h->ahead_back = std::min(2 * h->ahead_back, 1024);
+    h->ahead_good = 0;
+  } else if (++h->ahead_good >= h->ahead_back) {
+    h->ahead_back = 16;
+    h->ahead_good = 0;
+  }
 }
 
 template <int P>
@@ -1041,7 +1081,7 @@ nnp_status forward(nnp_handle* h, int n_struct, const int64_t* offs, const void*
   if ((st = fwd_buffers<P>(h, cm, n_struct, bufs))) return st;
   int layout = list_layout<P>(h);
   for (int attempt = 0; attempt < 8; ++attempt) {
-    const bool ahead = attempt == 0 && may_run_ahead<P>(h, 0, 1, n, layout);
+    const bool ahead = attempt == 0 && may_run_ahead<P>(h, 0, 1, cm.B, layout);
     if (ahead) {
       h->lcap = cm.bin.clip = std::min(h->lcap_next, h->cap);
       cm.bin.host_flags = nullptr;  // the network pass reports
@@ -1059,6 +1099,7 @@ nnp_status forward(nnp_handle* h, int n_struct, const int64_t* offs, const void*
     const bool synced = energy_host || h->prof;
     const int r = check_flags(h, stream, cm, &st, ahead, ahead && !synced);
     if (r < 0) return st;
+    if (ahead && n > AHEAD_ANY_ROWS_ATOMS) ran_ahead(h, r != 0);
     if (ahead && r == 0) return evaluated(h, mk, energy_host, remember, synced, stream);
     if (ahead) mk.restart(1);  // after the sort
     if (r == 1) continue;  // a capacity grew: rebuild the neighbour list
@@ -1154,7 +1195,7 @@ nnp_status forward_skin(nnp_handle* h, int64_t n, const void* pos_v, const int32
       h->cap = (nc + 15) / 16 * 16;
       continue;  // the next round re-gathers (unchanged) and refreshes into the larger rows
     }
-    set_lcap(h, cm.layout);
+    set_lcap(h, cm.B, cm.layout);
     mk.mark("neighbors");
     return evaluate<P>(h, cm, mk, bufs, 1, pos, types, energies_dev, nullptr, nullptr, f_v, stream, false);
   }

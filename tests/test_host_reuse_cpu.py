@@ -27,8 +27,8 @@ L = nnp.load_library()
 pot = nnp.Potential(*water_potential(), precision="fp64")
 
 class Batch:
-    def __init__(self, side, seed):
-        b = synth.water_box(side, seed)
+    def __init__(self, side, seed, stretch=1.0):
+        b = synth.water_box(side, seed, spacing=synth.WATER_SPACING * stretch)
         self.n, self.pos, self.types = b.n_atoms, b.pos.copy(), b.types.astype(np.int32)
         self.offs, self.box = (C.c_int64 * 2)(0, b.n_atoms), (C.c_double * 3)(*b.box)
     def args(self):
@@ -115,4 +115,73 @@ for rows in (90, 90, 110):
     assert a.forward() == 0
     assert list(pot.timings()) == stages, (rows, pot.timings())
 assert fake.fake_launches(b"k_mlp") == n + 2
+""")
+
+
+AHEAD = """
+pot = nnp.Potential(*water_potential(), precision="fp64")
+def forward(batch):  # whether the call launched its passes before it saw the flags
+    n, m = fake.fake_launches(b"k_max_count"), fake.fake_launches(b"k_mlp")
+    assert batch.forward() == 0
+    return fake.fake_launches(b"k_max_count") == n, fake.fake_launches(b"k_mlp") - m
+ONCE, WAITED, TWICE = (True, 1), (False, 1), (False, 2)
+fake.fake_lds.restype, fake.fake_lds.argtypes = C.c_size_t, [C.c_char_p]
+fake.fake_rows(100)
+"""
+
+
+def test_a_denser_batch_waits_for_its_rows(fake):
+    _run(fake, AHEAD + """
+dense = Batch(6, 4, 0.95)
+assert forward(a) == WAITED and forward(a) == ONCE  # 100 rows for the first time, then known
+fake.fake_rows(115)
+assert forward(dense) == WAITED and forward(dense) == ONCE
+fake.fake_rows(100)
+assert forward(a) == ONCE and forward(dense) == ONCE  # small batches: the longer rows cost nothing
+""")
+
+
+def test_a_sparser_large_batch_waits_for_its_rows(fake):
+    _run(fake, AHEAD + """
+large, sparse = Batch(18, 5), Batch(18, 6, 1.1)
+assert forward(large) == WAITED and forward(large) == ONCE
+fake.fake_rows(80)
+assert forward(sparse) == WAITED and forward(sparse) == ONCE
+""")
+
+
+def test_a_large_batch_gives_up_longer_rows_at_once(fake):
+    """Rows of a clustered box (the same mean density) are kept for one call."""
+    _run(fake, AHEAD + """
+large = Batch(18, 5)
+assert forward(large) == WAITED and forward(large) == ONCE
+own = fake.fake_lds(b"k_triplet")
+pot.set_list_layout("compact")  # (waits: no run ahead)
+fake.fake_rows(190)
+forward(large)
+pot.set_list_layout("padded")
+fake.fake_rows(100)
+assert forward(large) == ONCE and fake.fake_lds(b"k_triplet") > own
+assert forward(large) == ONCE and fake.fake_lds(b"k_triplet") == own
+""")
+
+
+def test_large_batches_wait_after_a_miss(fake):
+    """A call whose rows outgrew the capacity pays for its passes twice: the next 16
+    wait, twice as many after the next such call.  A small batch gains more by running
+    ahead than a miss in 16 calls costs it."""
+    _run(fake, AHEAD + """
+large = Batch(18, 5)
+assert forward(large) == WAITED and forward(large) == ONCE
+for waits in (16, 32):
+    fake.fake_rows(100 + waits // 2)
+    assert forward(large) == TWICE
+    for k in range(waits):
+        assert forward(large) == WAITED, k
+    assert forward(large) == ONCE
+fake.fake_rows(100)
+pot = nnp.Potential(*water_potential(), precision="fp64")
+assert forward(a) == WAITED and forward(a) == ONCE
+fake.fake_rows(110)
+assert forward(a) == TWICE and forward(a) == ONCE
 """)
