@@ -437,12 +437,18 @@ double mean_neighbors(const nnp_handle* h, const Batch& B) {
 // force pass of 98,304 water atoms, polynomials against exponentials, at mean
 // counts of 91: 1.05 / 1.46 against 1.20 / 1.51 ms, 68: 0.79 / 1.08 against 0.85 /
 // 1.03, 52: 0.68 / 0.88 against 0.69 / 0.81, 37: 0.54 / 0.72 against 0.53 / 0.64;
-// 1.5M fcc atoms (18): 3.70 / 5.16 against 3.42 / 4.19.  Three elements (91, the
-// kernels of any (q, n)): 0.236 / 0.433 against 0.269 / 0.417.  By the mean density
-// and not by the rows, so that a call's results do not turn on the calls before it.
+// 1.5M fcc atoms (18): 3.70 / 5.16 against 3.42 / 4.19.  Force-adjoint pass of 41,472
+// atoms at 45, 68, 91: 388, 516, 651 against 378, 519, 685 us.  Other tables, 41,472 atoms
+// at 45 and 91:
+//   two etas, any (q, n) (three elements): SF 403, 617 against 445, 716 us, force 713,
+//     1,148 against 661, 1,112, force-adjoint 696, 1,101 against 1,067, 1,704;
+//   four etas (60 coefficients): SF 603, 989 against 526, 871, force 831, 1,634 against
+//     676, 1,261, force-adjoint 1,211, 2,143 against 1,059, 1,869: never.
+// By the mean density and not by the rows, so that a call's results do not turn on the
+// calls before it.
 constexpr double POLY_MIN_SF = 45.0, POLY_MIN_FORCE = 80.0;
 int poly_modes(const nnp_handle* h, const Batch& B) {
-  if (!h->xpoly) return 0;
+  if (!h->xpoly || h->variant == 2) return 0;
   const double mean = mean_neighbors(h, B);
   return (mean >= POLY_MIN_SF ? 1 : 0) | (mean >= POLY_MIN_FORCE && h->variant == 0 ? 2 : 0) |
          (mean >= POLY_MIN_FORCE ? 4 : 0);

@@ -105,7 +105,8 @@ struct TripArgs {
   // pass tests the pairs.  pm_stride >= ceil(pair_step_bound(lcap, n_el) / 32).
   unsigned* pm;
   int pm_stride;
-  int poly;                  // FP64: bit m: mode m takes the table's X_n polynomials (DevTab::xpoly)
+  int poly;                  // FP64: bit m: mode m takes the table's X_n polynomials (DevTab::xpoly);
+                             // built for two etas, in the force mode for the water mask
 };
 
 // Most steps the one-wave pair walk can take for a centre with m neighbours

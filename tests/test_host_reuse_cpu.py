@@ -185,3 +185,25 @@ assert forward(a) == WAITED and forward(a) == ONCE
 fake.fake_rows(110)
 assert forward(a) == TWICE and forward(a) == ONCE
 """)
+
+
+def test_four_eta_tables_keep_the_exponentials(fake):
+    """FP64 passes of tables with more than two angular etas: the polynomials' 60
+    coefficients cost more than the exponentials they replace, at every density."""
+    _run(fake, AHEAD + """
+def table(etas):
+    t = []
+    for c in (0, 1):
+        t += [synth.SF(c, 2, (nb,), 0.01) for nb in (0, 1)]
+        for cls in synth.PAIR_CLASSES:
+            t += [synth.SF(c, 3, cls, eta, 0.0, 2.0, 1.0) for eta in etas]
+    return t, synth.xavier_nets(synth.sf_counts(t), 5)
+poly = lambda: fake.fake_launches(b"Lb1ELb0EEEv")  # k_triplet<..., POLY, not WIDE>
+for etas, used in (((0.001, 0.03), True), ((0.001, 0.01, 0.03), False), ((0.001, 0.01, 0.02, 0.03), False)):
+    pot = nnp.Potential(*table(etas), precision="fp64")
+    n, m = poly(), fake.fake_launches(b"k_triplet")
+    forward(a)
+    a.backward()
+    assert fake.fake_launches(b"k_triplet") > m
+    assert (poly() > n) == used, etas
+""")
