@@ -61,7 +61,8 @@ struct nnp_handle {
   std::string err;
   double rc = 0.0;
   int variant = 0;                      // triplet-kernel instantiation (see launch_mode)
-  bool xpoly = false;                   // tab_d.xpoly reaches XP_MAX_ERROR for every angular eta
+  bool xpoly = false;                   // tab_d.xpoly reaches XP_MAX_ERROR for every angular eta of a
+                                        // table whose passes may take it
   std::vector<int> n_sf;                // per element
   std::vector<std::vector<int>> sizes;  // per element layer widths
   std::vector<double> params;           // flat caller layout
@@ -448,7 +449,7 @@ double mean_neighbors(const nnp_handle* h, const Batch& B) {
 // calls before it.
 constexpr double POLY_MIN_SF = 45.0, POLY_MIN_FORCE = 80.0;
 int poly_modes(const nnp_handle* h, const Batch& B) {
-  if (!h->xpoly || h->variant == 2) return 0;
+  if (!h->xpoly) return 0;
   const double mean = mean_neighbors(h, B);
   return (mean >= POLY_MIN_SF ? 1 : 0) | (mean >= POLY_MIN_FORCE && h->variant == 0 ? 2 : 0) |
          (mean >= POLY_MIN_FORCE ? 4 : 0);
@@ -1435,8 +1436,9 @@ nnp_status md_run(nnp_handle* h, int64_t n, void* pos_v, void* vel_v, void* f_v,
 // --------------------------------------------------------------- create
 // Interpolates X(t) = (1 + cos(pi sqrt t)) / 2 e^{-b t} at the Chebyshev points
 // of [0, 1] (Newton's divided differences, then the monomial basis in t' - 1/2,
-// in long double) to degree DEG and returns the largest error of the rounded
-// coefficients' polynomial on a fine grid.  t' = t / stretch = r^2 inv_rc2 is what the
+// in long double) to degree DEG and returns whether the rounded coefficients'
+// polynomial is within max_error at every fourth of the way between two extrema of the
+// error (which lie between the Chebyshev points).  t' = t / stretch = r^2 inv_rc2 is what the
 // kernels form of r^2, with the rounding of 1 / rc^2 in it: taken for t it would move
 // every term the same way.  At b = eta rc^2 = 1.08 (the water
 // table's larger eta) degree 14 is within 5e-17, and it passes XP_MAX_ERROR
@@ -1446,7 +1448,7 @@ nnp_status md_run(nnp_handle* h, int64_t n, void* pos_v, void* vel_v, void* f_v,
 // error in an SF's sum over a box, where powers of t' had up to 8e-16.)
 constexpr double XP_MAX_ERROR = 3e-16, XP_LOW_ERROR = 1.2e-16;
 template <int DEG>
-double fit_xpoly(long double b, long double stretch, double* c) {
+bool fit_xpoly(long double b, long double stretch, double max_error, double* c) {
   using L = long double;
   const L pi = 3.14159265358979323846264338327950288L;
   auto X = [&](L t) { return (1.0L + cosl(pi * sqrtl(t))) / 2.0L * expl(-b * t); };
@@ -1464,15 +1466,13 @@ double fit_xpoly(long double b, long double stretch, double* c) {
     p[0] = d[i] - p[0] * t[i];
   }
   for (int i = 0; i <= XP_DEG; ++i) c[i] = i < N ? (double)p[i] : 0.0;
-  L worst = 0;
-  for (int g = 0; g <= 200; ++g) {  // over ten points between two zeros of the error
-    const L x = g / 200.0L;
+  for (int g = 0; g <= 4 * N; ++g) {
+    const L x = cosl(pi * g / (4 * N)) / 2;
     L v = c[N - 1];
-    for (int i = N - 2; i >= 0; --i) v = v * (x - 0.5L) + (L)c[i];
-    const L e = fabsl(v - X(stretch * x));
-    if (!(e <= worst)) worst = e;  // NaN too
+    for (int i = N - 2; i >= 0; --i) v = v * x + (L)c[i];
+    if (!(fabsl(v - X(stretch * (x + 0.5L))) <= max_error)) return false;  // NaN too
   }
-  return (double)worst;
+  return true;
 }
 
 nnp_status build_table(nnp_handle* h, int n_el, int n_sf, const nnp_sf* sf, const nnp_net* nets) {
@@ -1559,14 +1559,22 @@ nnp_status build_table(nnp_handle* h, int n_el, int n_sf, const nnp_sf* sf, cons
   t.inv_rc2_lo = std::isfinite(t.inv_rc2) ? (double)(1 / rc2 - t.inv_rc2) : 0.0;
   const long double rc2_rounded = 1 / (long double)t.inv_rc2;
   int ne_max = 1;
-  h->xpoly = h->prec == NNP_FP64;
   for (int e = 0; e < n_el; ++e) {
     t.n_sf[e] = count[e];
     t.n_eta[e] = (int)etas[e].size();
     for (size_t x = 0; x < etas[e].size(); ++x) {
       t.aeta[e][x] = etas[e][x];
       t.aeta2[e][x] = etas[e][x] * 1.4426950408889634074;
-      if (!h->xpoly) continue;
+    }
+    ne_max = std::max(ne_max, t.n_eta[e]);
+  }
+  if (ne_max > 2) h->variant = 2;
+  else if ((qn_mask & ~QN_WATER) == 0) h->variant = 0;
+  else h->variant = 1;
+  // the polynomials of the etas, for tables whose passes may take them (poly_modes)
+  h->xpoly = h->prec == NNP_FP64 && h->variant != 2 && !h->has_wide;
+  for (int e = 0; e < n_el; ++e)
+    for (size_t x = 0; x < etas[e].size() && h->xpoly; ++x) {
       bool known = false;  // an eta of an earlier element
       for (int f = 0; f < e && !known; ++f)
         for (size_t y = 0; y < etas[f].size() && !known; ++y)
@@ -1575,15 +1583,10 @@ nnp_status build_table(nnp_handle* h, int n_el, int n_sf, const nnp_sf* sf, cons
             t.xhigh[e][x] = t.xhigh[f][y];
           }
       if (known) continue;
-      const long double b = etas[e][x] * rc2;
-      t.xhigh[e][x] = fit_xpoly<XP_LOW>(b, rc2_rounded / rc2, t.xpoly[e][x]) <= XP_LOW_ERROR ? 0 : 1;
-      if (t.xhigh[e][x] && !(fit_xpoly<XP_DEG>(b, rc2_rounded / rc2, t.xpoly[e][x]) <= XP_MAX_ERROR)) h->xpoly = false;
+      const long double b = etas[e][x] * rc2, stretch = rc2_rounded / rc2;
+      t.xhigh[e][x] = fit_xpoly<XP_LOW>(b, stretch, XP_LOW_ERROR, t.xpoly[e][x]) ? 0 : 1;
+      if (t.xhigh[e][x]) h->xpoly = fit_xpoly<XP_DEG>(b, stretch, XP_MAX_ERROR, t.xpoly[e][x]);
     }
-    ne_max = std::max(ne_max, t.n_eta[e]);
-  }
-  if (ne_max > 2) h->variant = 2;
-  else if ((qn_mask & ~QN_WATER) == 0) h->variant = 0;
-  else h->variant = 1;
   h->n_sf = count;
   // networks
   h->sizes.clear();
