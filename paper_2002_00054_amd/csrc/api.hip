@@ -702,9 +702,10 @@ int check_flags(nnp_handle* h, hipStream_t stream, Common& cm, nnp_status* st, b
 
 // Level of the pair passes of modes mode_a and mode_b (0 SF, 1 force, 2
 // force-adjoint product): *flat for a thread per centre, else *wpc waves per
-// centre.  A thread per centre when asked for or when the table holds wide
-// angular SFs; the wave levels when asked for, refused before any launch if
-// an atom has more neighbours than they can stage in LDS.  NNP_PAR_AUTO
+// centre.  A thread per centre when asked for; the wave levels when asked for,
+// refused before any launch if an atom has more neighbours than they can stage in
+// LDS.  Tables with wide angular SFs take one wave per centre in FP64 and FP32, a
+// thread per centre in the BF16 form and for an atom beyond the LDS.  NNP_PAR_AUTO
 // takes one wave per centre (measured the fastest on both workloads, short
 // rows included); for an atom beyond its LDS, two waves per centre (a
 // workgroup then holds two centres, not four), and beyond that the thread

@@ -70,7 +70,7 @@ __global__ void __launch_bounds__(256) k_bin(int64_t n, const TIn* __restrict__ 
 // those sums, then each block scanning its keys from its offset.
 constexpr int SCAN_PER = 4096;  // keys per block (1024 threads x 4)
 constexpr int SCAN_ONE_KEYS = 8 * SCAN_PER;         // scanned by one block up to here
-constexpr int SMALL_ATOMS = 4096, SMALL_KEYS = 4096;  // sorted by one block up to here (64 KB of LDS)
+constexpr int SMALL_ATOMS = 4096, SMALL_KEYS = 4096;  // sorted by one block up to here (50 KB of LDS)
 
 // Exclusive scan of v over a 1024-thread block; *total receives the sum.
 __device__ inline int block_exclusive_scan(int v, int* sh, int* total) {
@@ -804,12 +804,15 @@ void launch_bin_sort(const BinArgs& a, const TIn* pos, hipStream_t stream) {
 template void launch_bin_sort<float>(const BinArgs&, const float*, hipStream_t);
 template void launch_bin_sort<double>(const BinArgs&, const double*, hipStream_t);
 
-// Batches of at most this many cells reduce the largest count inside the build,
-// one launch fewer.  Each cell then pays two atomics on one address and a
-// device-wide fence (about 0.15 us in turn: 512 cells 25 us, 4,096 cells 600 us);
-// larger batches keep per-cell counts and the grid of k_max_count, whose blocks
-// take 4,096 cells each.
-constexpr int DIRECT_MAX_CELLS = 32;
+// Builds of at most this many workgroups (some 128 atoms: cells times neighbor_split)
+// reduce the largest count themselves, one launch fewer; calls that run ahead do not
+// get here (the network pass does it), so these are first calls, compact rows, the
+// stored Jacobian and the thread level: 108 fcc atoms with compact rows 100 us, 113 with
+// k_max_count, at the thread level 686 and 696.  Each workgroup pays two atomics on one
+// address and a device-wide fence (about 0.15 us in turn: 512 of them 25 us, 4,096 600 us);
+// larger builds keep per-workgroup counts and the grid of k_max_count, whose blocks take
+// 4,096 each.
+constexpr int DIRECT_MAX_BLOCKS = 32;
 
 // A cell's centres are shared among several workgroups, as long as all of them
 // fit on the 256 CUs at once (six each) and a wave keeps a centre: one workgroup
@@ -830,7 +833,7 @@ void launch_neighbors_as(const BinArgs& a, double rc, int cap, E* nbr, int4* nnb
                          const int* roff = nullptr) {
   if (a.n == 0) return;
   const int split = neighbor_split(a.n, a.total_cells), blocks = a.total_cells * split;
-  const bool small = a.host_flags && blocks <= DIRECT_MAX_CELLS;
+  const bool small = a.host_flags && blocks <= DIRECT_MAX_BLOCKS;
   if (small || split > 1)
     hipLaunchKernelGGL((k_neighbors<E, true>), dim3((unsigned)a.total_cells, (unsigned)split), dim3(256), 0, stream, a.pos4,
                        a.st, a.n_struct, a.start, a.n_el, a.total_cells, rc * rc, cap, std::min(cap, a.clip), nbr, nnb, a.flags, cmax, roff,
