@@ -1438,8 +1438,8 @@ nnp_status md_run(nnp_handle* h, int64_t n, void* pos_v, void* vel_v, void* f_v,
 // Interpolates X(t) = (1 + cos(pi sqrt t)) / 2 e^{-b t} at the Chebyshev points
 // of [0, 1] (Newton's divided differences, then the monomial basis in t' - 1/2,
 // in long double) to degree DEG and returns whether the rounded coefficients'
-// polynomial is within max_error at every fourth of the way between two extrema of the
-// error (which lie between the Chebyshev points).  t' = t / stretch = r^2 inv_rc2 is what the
+// polynomial is within max_error at the extrema of the interpolation's error (the ends,
+// and one between each two Chebyshev points).  t' = t / stretch = r^2 inv_rc2 is what the
 // kernels form of r^2, with the rounding of 1 / rc^2 in it: taken for t it would move
 // every term the same way.  At b = eta rc^2 = 1.08 (the water
 // table's larger eta) degree 14 is within 5e-17, and it passes XP_MAX_ERROR
@@ -1467,8 +1467,8 @@ bool fit_xpoly(long double b, long double stretch, double max_error, double* c) 
     p[0] = d[i] - p[0] * t[i];
   }
   for (int i = 0; i <= XP_DEG; ++i) c[i] = i < N ? (double)p[i] : 0.0;
-  for (int g = 0; g <= 4 * N; ++g) {
-    const L x = cosl(pi * g / (4 * N)) / 2;
+  for (int g = 0; g <= N; ++g) {
+    const L x = cosl(pi * g / N) / 2;
     L v = c[N - 1];
     for (int i = N - 2; i >= 0; --i) v = v * x + (L)c[i];
     if (!(fabsl(v - X(stretch * (x + 0.5L))) <= max_error)) return false;  // NaN too
