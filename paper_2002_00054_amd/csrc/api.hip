@@ -765,7 +765,9 @@ bool may_run_ahead(nnp_handle* h, int mode_a, int mode_b, const Batch& B, int la
 
 // A batch that fills the machine ran ahead, in vain (missed) or not.  After one in vain
 // the next 16 calls wait, and twice as many (up to 1,024) after another one that follows
-// before as many have run well.  (Smaller ones lose 60 us by a miss and 12 by a wait.)
+// before as many have run well.  Smaller batches lose less by a miss than by 16 waits of 12
+// us: one call in twenty on a clustered box of 1,536 atoms takes 106 us on average running
+// ahead, 114 waiting.
 void ran_ahead(nnp_handle* h, bool missed) {
   if (missed) {
     h->ahead_wait = h->ahead_back;

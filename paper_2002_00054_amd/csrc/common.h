@@ -251,9 +251,9 @@ __device__ inline float rsqrt_t(float s) { return __builtin_amdgcn_rsqf(s); }
 // Cutoff polynomial in t = r^2/rc^2 per arithmetic type: interpolants of
 // fc = (1 + cos(pi sqrt(t)))/2 at the Chebyshev points (gen_cutoff.py).  FP64:
 // degree 10 in powers of t - 1/2, max error 5e-17 (fc) and 4e-15 (dfc/dt)
-// before rounding, rounded for the least mean error.  FP32: degree 6 in powers of t, max error 5.5e-9, below
-// FP32 rounding.  Both are several terms shorter than the Taylor series of the
-// same accuracy.
+// before the evaluation's rounding, coefficients rounded for the least mean error.
+// FP32: degree 6 in powers of t, max error 5.5e-9, below FP32 rounding.  Both are
+// several terms shorter than the Taylor series of the same accuracy.
 template <class T> struct FcPoly;
 template <> struct FcPoly<double> {
   static constexpr int D = 10;
